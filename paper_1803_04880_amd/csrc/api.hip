@@ -17,7 +17,6 @@ hipError_t launch_inv(int L, int C1, bool u8out, const int16_t *llin, const int1
                       void *out, const StageParams &P, hipStream_t s);
 hipError_t launch_ctr(const uint8_t *in, uint8_t *out, uint64_t nbytes, const AesKey &key,
                       uint64_t first_block, hipStream_t s);
-int fwd_waves_per_cu(int L, int C1, bool u8in);
 int inv_waves_per_cu(int L, int C1, bool u8out);
 int inv_split_waves_per_cu(int L, int C1, bool all_fast);
 bool inv_stage_split_ok(const StageParams &P);
@@ -127,17 +126,17 @@ void level_offsets(const Geometry &g, uint32_t l, int64_t *hl, int64_t *lh, int6
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-// Wavefronts the current device keeps resident at once for the kernel of a
-// stage: compute units x resident wavefronts per CU (queried once per device
+// Wavefronts the current device keeps resident at once for the inverse kernel
+// of a stage: compute units x resident wavefronts per CU (queried once per device
 // and kernel variant; falls back to 256 x 16 if the queries fail).  split:
 // 0 for the one-launch kernels, 1 / 2 for the split restore's packed kernel
 // with every wavefront FAST / not.
-int64_t device_slots(bool forward, int L, int C1, bool bytes, int split = 0) {
-  constexpr int kDev = 16, kVar = 2 * 5 * 3 * 2 * 2;
+int64_t device_slots(int L, int C1, bool bytes, int split = 0) {
+  constexpr int kDev = 16, kVar = 5 * 3 * 2 * 2;
   static std::atomic<int> cache[kDev][kVar];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDev) dev = -1;
-  const int var = (((forward ? 1 : 0) * 5 + L) * 3 + split) * 4 + (C1 == 16 ? 2 : 0) + (bytes ? 1 : 0);
+  const int var = (L * 3 + split) * 4 + (C1 == 16 ? 2 : 0) + (bytes ? 1 : 0);
   if (dev >= 0) {
     const int v = cache[dev][var].load(std::memory_order_relaxed);
     if (v > 0) return v;
@@ -145,9 +144,8 @@ int64_t device_slots(bool forward, int L, int C1, bool bytes, int split = 0) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess)
     cus = 0;
-  const int per_cu = forward ? fwd_waves_per_cu(L, C1, bytes)
-                     : split ? inv_split_waves_per_cu(L, C1, split == 1)
-                             : inv_waves_per_cu(L, C1, bytes);
+  const int per_cu = split ? inv_split_waves_per_cu(L, C1, split == 1)
+                           : inv_waves_per_cu(L, C1, bytes);
   const int slots = (cus > 0 && per_cu > 0) ? cus * per_cu : 256 * 16;
   if (dev >= 0) cache[dev][var].store(slots, std::memory_order_relaxed);
   return slots;
@@ -171,6 +169,24 @@ int64_t device_simds() {
   return simds;
 }
 
+// Rows of a forward segment.  A segment recomputes 2^(L+1) + 2^L - 3 rows, so
+// taller is less work, but every wavefront is one serial stream: a launch of
+// its own wants about 940 of them (at one level, where the cipher counts
+// most, 1536) before its segments grow past one unit.  The tallest worth it,
+// by level (measured, us at 4096 columns, 16 / 64 MiB, or 32768, 256 MiB):
+//   1: 24 rows 24.9 / 68.6 / 228 (8: 25.0 / 67.9 / 252);
+//   2: 16 rows 16.6 / 44.8 / 179, 32: 19.5 / 46.7 / 168;
+//   3: 96 rows (8 columns a lane) 46.9 at 64 MiB, 48: 47.7, 16: 56.2; at 16
+//      columns 24 rows 176 at 256 MiB (32: 182, 96: 208);
+//   4: 96 rows 53.7 at 64 MiB (64: 60.9), 64 rows 198 at 256 MiB (96: 214).
+int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells, bool alone) {
+  const bool large = cells >= (uint64_t(1) << 27);
+  const int most = L == 1 ? 24 : L == 2 ? (large ? 32 : 16) : L == 3 ? (C1 == 16 ? 24 : 96) : large ? 64 : 96;
+  const int64_t want = alone ? int64_t(n_win) * H / (L == 1 ? 1536 : 940) : most;
+  const int rows = round_up(int(std::min<int64_t>(std::max<int64_t>(want, 1), most)), 1 << L);
+  return std::min(rows, fwd_max_rows(L, C1));
+}
+
 // Fill stage s's parameters.  forward selects the halo shape of the direction;
 // alone: the stage runs as its own launch (not as one item of a batch that
 // shares the device).
@@ -179,12 +195,13 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   std::memset(P, 0, sizeof(*P));
   const int lv0 = kMaxFused * s;  // global level of the stage input
   const int L = int(std::min<uint32_t>(kMaxFused, g.levels - lv0));
-  // Default columns per lane: 16 for a stage of at least 64 Mi elements (the
-  // per-row work is spread over twice the columns and the device stays full
-  // at two wavefronts per SIMD; 256 MiB at three levels: forward 237 -> 224
-  // us, inverse 248 -> 227 us in its two-launch form), else 8 (more, shorter
-  // streams for smaller stages).
-  const bool wide = uint64_t(g.h[lv0]) * g.w[lv0] >= (uint64_t(1) << 26);
+  // Default columns per lane: 8, but 16 (the per-row work spread over twice
+  // the columns) for an inverse stage of at least 64 Mi elements (256 MiB at
+  // three levels 248 -> 227 us), and a forward of three levels and 128 Mi
+  // (176 against 181 us at 256 MiB; 46.2 against 46.9 at 64 MiB, and one and
+  // two levels are as fast at 8: 228, 168 against 227, 169).
+  const uint64_t cells = uint64_t(g.h[lv0]) * g.w[lv0];
+  const bool wide = forward ? L == 3 && cells >= (uint64_t(1) << 27) : cells >= (uint64_t(1) << 26);
   int C1 = (launch && launch->lane_cols) ? int(launch->lane_cols) : (wide ? 16 : 8);
   if (C1 != 8 && C1 != 16) return DWTFRAG_EINVAL;
   if (L == 4) C1 = 16;
@@ -209,6 +226,10 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
     P->n_win = 1;
   } else {
     P->own_w = span - hl - hr;
+    // A forward window owns whole 128-byte lines of its level-1 band rows:
+    // lines that two windows share are written in parts (256 MiB at three
+    // levels: 448 of 512 columns 185 us, 496 columns 251 us).
+    if (forward) P->own_w = P->own_w / 128 * 128;
     P->n_win = (P->W + P->own_w - 1) / P->own_w;
   }
   P->halo_l = hl;
@@ -226,8 +247,12 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   P->units = (P->H + unit - 1) / unit;
   int64_t n_seg;
   if (launch && launch->seg_rows) {
-    const int own_h = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
+    int own_h = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
+    if (forward) own_h = std::min(own_h, fwd_max_rows(L, C1));
     n_seg = (int64_t(P->H) + own_h - 1) / own_h;
+  } else if (forward) {
+    const int rows = fwd_seg_rows(L, C1, P->n_win, P->H, cells, alone);
+    n_seg = (int64_t(P->H) + rows - 1) / rows;
   } else {
     // one round of resident wavefronts: as many segments as fill the device
     // once, each at least two units long (halo work stays below the owned).
@@ -241,7 +266,7 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
     // kernel's when the finished plan turns out not to run split.
     const int min_units = (alone && int64_t(P->units) * P->n_win <= device_simds()) ? 1 : 2;
     const auto segments = [&](int split) {
-      const int64_t slots = device_slots(forward, L, C1, s == 0, split);
+      const int64_t slots = device_slots(L, C1, s == 0, split);
       const int64_t k = std::max<int64_t>(1, slots / P->n_win);
       return std::min<int64_t>(k, std::max(1, P->units / min_units));
     };

@@ -30,6 +30,11 @@ struct BatchItem {
   int32_t pad;
 };
 
+// The item table as the kernels read it: by scalar loads (it is written
+// before the launch).
+using ConstItem = const __attribute__((address_space(4))) BatchItem;
+__device__ __forceinline__ ConstItem *const_items(const BatchItem *items) { return (ConstItem *)items; }
+
 // Queue counters of one direction: [0] next tile, [1] finished workgroups.
 struct BatchCounters {
   unsigned int head, done;

@@ -136,22 +136,51 @@ static __constant__ AesTables c_aes = make_aes_tables();
 // The four byte-rotated T-tables (1024 words) into LDS, loaded by the whole
 // block; the caller synchronises the block afterwards.
 __device__ __forceinline__ void load_aes_te(uint32_t *te) {
-  for (int i = threadIdx.x; i < 1024; i += blockDim.x) {
-    const uint32_t v = c_aes.te0[i & 255];
-    const int r = 8 * (i >> 8);
-    te[i] = r ? ((v << r) | (v >> (32 - r))) : v;
+  for (int i = threadIdx.x; i < 256; i += blockDim.x) {
+    const uint32_t v = c_aes.te0[i];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) te[256 * r + i] = __builtin_amdgcn_alignbit(v, v, (32 - 8 * r) & 31);
   }
 }
 
 // Word i (< kKeyWords) of the LDS key block: 44 round-key words, then the
 // nonce's two 64-bit halves as low / high words.
-__device__ __forceinline__ uint32_t key_word(const AesKey &key, int i) {
+template <class K> __device__ __forceinline__ uint32_t key_word(K &key, int i) {
   if (i < 44) return key.rk[i];
   if (i == 44) return uint32_t(key.nonce_hi);
   if (i == 45) return uint32_t(key.nonce_hi >> 32);
   if (i == 46) return uint32_t(key.nonce_lo);
   return uint32_t(key.nonce_lo >> 32);
 }
+
+// Tables and key words of a block of 64 or 256 threads that uses one key, in
+// two steps: the loads, and the writes to LDS once they have arrived (the
+// block then synchronises).  Loads issued in between are not waited for.
+struct AesLoad {
+  uint32_t t[4], k;
+  __device__ __forceinline__ void issue(const AesKey &key) {
+    const int i = int(threadIdx.x);
+    t[0] = c_aes.te0[i];
+    if (blockDim.x == 64) {
+#pragma unroll
+      for (int j = 1; j < 4; ++j) t[j] = c_aes.te0[64 * j + i];
+    }
+    k = i < kKeyWords ? key_word(key, i) : 0;
+  }
+  __device__ __forceinline__ void finish(uint32_t *te, uint32_t *kw) const {
+    const int i = int(threadIdx.x);
+    put(te + i, t[0]);
+    if (blockDim.x == 64) {
+#pragma unroll
+      for (int j = 1; j < 4; ++j) put(te + 64 * j + i, t[j]);
+    }
+    if (i < kKeyWords) kw[i] = k;
+  }
+  __device__ __forceinline__ static void put(uint32_t *te, uint32_t v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) te[256 * r] = __builtin_amdgcn_alignbit(v, v, (32 - 8 * r) & 31);
+  }
+};
 
 // Tables and key words together, for a block that uses one key.
 __device__ __forceinline__ void load_aes_tables(uint32_t *te, uint32_t *kw, const AesKey &key) {
@@ -182,16 +211,35 @@ struct StageParams {
   AesKey key;
 };
 
+// Forward kernel: the rows of a segment are limited by the keystream that a
+// wavefront holds in LDS: 16 LL rows (8 at four levels, and at one level of
+// 16 columns a lane), under 9 KiB, so that four workgroups fit a compute
+// unit.  A row takes its elements' blocks and two cut ones.
+constexpr int fwd_ll_rows(int L, int C1) { return L == 4 || (L == 1 && C1 == 16) ? 8 : 16; }
+constexpr int fwd_max_rows(int L, int C1) { return fwd_ll_rows(L, C1) << L; }
+constexpr int fwd_ks_words(int L, int C1) {
+  return fwd_ll_rows(L, C1) * (64 * C1 / (8 << L) + 2) * 4;
+}
+// Wavefronts per workgroup of a forward launch: one where the whole grid is
+// about a wavefront per compute unit (each then has an LDS of its own for
+// the AES lookups), else four.
+constexpr int fwd_block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBlock; }
+
+// A stage's parameters as the kernels take them (SP below): a kernel argument,
+// or an entry of a batch's item table, read through the constant address
+// space so that it comes by scalar loads.
+using ConstStage = const __attribute__((address_space(4))) StageParams;
+
 // First level-0 column of window win's lanes: the owned range minus the left
 // halo, from column 0 for the first window; the last window's lanes may start
 // further left (last_base) so that they end inside the row.
-__device__ __forceinline__ int window_base(const StageParams &P, int win) {
+template <class SP> __device__ __forceinline__ int window_base(SP &P, int win) {
   if (win == 0) return 0;
   return win == P.n_win - 1 ? P.last_base : win * P.own_w - P.halo_l;
 }
 
 // First level-0 row of segment s (s == n_seg gives units * unit_rows).
-__device__ __forceinline__ int seg_start(const StageParams &P, int s) {
+template <class SP> __device__ __forceinline__ int seg_start(SP &P, int s) {
   return P.unit_rows * int((int64_t(s) * P.units) / P.n_seg);
 }
 
@@ -208,14 +256,21 @@ template <class T> __device__ __forceinline__ gptr<T> glob(T *p) { return (gptr<
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// A pointer that is the same in every lane, in scalar registers.
+template <class T> __device__ __forceinline__ T *uniform_ptr(T *p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<T *>(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(a)))) |
+                               (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(a >> 32)))) << 32));
+}
+
 // ------------------------------------------------------- wavefront taps --
 // wave_shl:1 -> lane i receives lane i+1; wave_shr:1 -> lane i receives
-// lane i-1 (the lane with no source receives 0).
+// lane i-1 (the lane with no source receives 0, or `none`).
 __device__ __forceinline__ int from_next_lane(int v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, false);
 }
-__device__ __forceinline__ int from_prev_lane(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, false);
+__device__ __forceinline__ int from_prev_lane(int v, int none = 0) {
+  return __builtin_amdgcn_update_dpp(none, v, 0x138, 0xF, 0xF, false);
 }
 
 __device__ __forceinline__ void wave_lds_sync() {

@@ -94,6 +94,31 @@ __device__ __forceinline__ void hfwd_pk(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[P
   for (int j = 0; j < P; ++j) O[j] = D[j];
 }
 
+// The same for a window whose lanes a row's ends cannot cut: column 0 can
+// only be lane 0's first, column N-1 only the last of the lane with `redge`
+// set.  The mirror then replaces what the neighbour lane would supply: lane
+// 0, which has no lane before it, keeps d(1) as d(-1) (in a window that does
+// not start at column 0 that lane is a halo lane), and the last lane takes
+// x(N-2) as x(N).
+template <int M>
+__device__ __forceinline__ void hfwd_pk_lanes(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[Pk<M>::P],
+                                              bool redge) {
+  constexpr int P = Pk<M>::P;
+  uint32_t nxt = uint32_t(from_next_lane(int(E[0])));
+  nxt = redge ? (M >= 2 ? E[P - 1] >> 16 : E[0]) : nxt;
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const uint32_t en = (j + 1 < P) ? align16(E[j + 1], E[j]) : (M >= 2 ? align16(nxt, E[j]) : nxt);
+    O[j] = pk_predict(O[j], E[j], en);
+  }
+  const uint32_t prv = uint32_t(from_prev_lane(int(O[P - 1]), int(M >= 2 ? O[0] << 16 : O[0])));
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const uint32_t dl = (j > 0) ? align16(O[j], O[j - 1]) : (M >= 2 ? align16(O[0], prv) : prv);
+    E[j] = pk_update(E[j], dl, O[j]);
+  }
+}
+
 template <int M>
 __device__ __forceinline__ void hfwd_pk_any(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[Pk<M>::P], int j0,
                                             int N, bool edge) {

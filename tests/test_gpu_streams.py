@@ -1,0 +1,81 @@
+"""GPU parity of the streaming kernels at the edges of what a wavefront covers.
+
+Widths around a lane's columns, a window's lanes and its owned columns;
+heights around the unit of 2^levels rows and a segment's rows; partial last
+rows that end inside any of them; every depth of a fused stage at both lane
+widths.  Integer work: fragments equal the oracle's byte for byte, and
+restore returns the input.
+"""
+import numpy as np
+import pytest
+
+from conftest import gpu_available
+
+pytestmark = pytest.mark.gpu
+
+if not gpu_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import torch  # noqa: E402
+
+import paper_1803_04880_amd as dwtfrag  # noqa: E402
+from oracle import fragment  # noqa: E402
+
+DEV = "cuda:0"
+
+
+def _check(n, width, levels, launch):
+    rng = np.random.default_rng([n, width, levels])
+    buf = rng.integers(0, 256, n, dtype=np.uint8)
+    key, nonce = rng.bytes(16), rng.bytes(16)
+    print(f"n={n} width={width} levels={levels} launch={launch}", flush=True)
+    x = torch.from_numpy(buf).to(DEV)
+    priv, pub = dwtfrag.protect(x, width, levels, key, nonce, launch=launch)
+    out = dwtfrag.restore(priv, pub, n, width, levels, key, nonce, launch=launch)
+    opriv, opub = fragment.protect(buf, width, levels, key, nonce)
+    assert priv.cpu().numpy().tobytes() == opriv
+    assert pub.cpu().numpy().tobytes() == opub
+    assert out.cpu().numpy().tobytes() == buf.tobytes()
+
+
+@pytest.mark.parametrize("levels,cols", [(1, 8), (2, 8), (3, 8), (1, 16), (2, 16), (3, 16), (4, 16)])
+@pytest.mark.parametrize("span", [1, 4])
+def test_window_edges(levels, cols, span):
+    """Rows ending at, before and after a lane, a window (64 lanes) and an
+    owned range (whole 128-column pieces of it)."""
+    if span == 1:
+        widths = [1, 2, 3, cols - 1, cols, cols + 1, 2 * cols, 9 * cols + 5]
+    else:
+        win, own = 64 * cols, (64 * cols - 48) // 128 * 128
+        widths = [win - 1, win, win + 1, win + cols, own + 8, 2 * own - 1, 2 * own, 2 * own + 7]
+    for i, width in enumerate(widths):
+        height = 37 + 5 * i
+        _check(height * width - (i % 3) * (width // 3), width, levels, (0, cols))
+
+
+@pytest.mark.parametrize("levels,cols", [(1, 8), (2, 8), (3, 8), (1, 16), (2, 16), (3, 16), (4, 16)])
+def test_segment_edges(levels, cols):
+    """Heights around one and two units, and around a segment's rows."""
+    unit = 1 << levels
+    width = 8 * cols + 3
+    for height in sorted({1, 2, unit - 1, unit, unit + 1, 2 * unit - 1, 2 * unit + 1, 4 * unit,
+                          4 * unit + 1, 9 * unit - 1, 9 * unit + 2}):
+        if height < 1:
+            continue
+        _check(height * width - (width // 2 if height % 2 else 0), width, levels, (0, cols))
+        _check(height * width, width - 3, levels, (4 * unit, cols))
+
+
+@pytest.mark.parametrize("width", [512, 1000, 1021])
+@pytest.mark.parametrize("levels", [1, 2, 3, 4])
+def test_partial_last_row(width, levels):
+    """The view's last row ends inside the first lane, a window, the last one."""
+    for rest in (1, 3, width // 2, width - 1):
+        _check(70 * width + rest, width, levels, None)
+
+
+@pytest.mark.parametrize("levels", [5, 6, 8])
+def test_deep_stages(levels):
+    """int16 stages behind the byte stage, at odd and even inner sizes."""
+    for width, height in ((2064, 530), (1037, 611)):
+        _check(width * height - 11, width, levels, None)
