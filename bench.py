@@ -69,8 +69,10 @@ def percentile(xs, q):
 
 
 # sources of the kernels and launch planning the plain protect / restore runs
-PLAIN_PATH_SOURCES = ("api.hip", "common.h", "fwd.h", "fwd.hip", "inv.hip", "lift.h", "pack.h")
-BATCH_PATH_SOURCES = PLAIN_PATH_SOURCES + ("batch.h", "batch.hip", "fwd_batch.hip")
+PLAIN_PATH_SOURCES = ("api.hip", "common.h", "fwd.h", "fwd.hip", "inv.h", "inv.hip",
+                      "lift.h", "pack.h")
+BATCH_PATH_SOURCES = PLAIN_PATH_SOURCES + ("batch.h", "batch.hip", "fwd_batch.hip",
+                                             "inv_batch.hip")
 
 
 def source_hash(sources=PLAIN_PATH_SOURCES) -> str:

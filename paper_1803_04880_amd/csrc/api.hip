@@ -3,7 +3,6 @@
 #include "dwtfrag.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <mutex>
 
@@ -17,10 +16,6 @@ hipError_t launch_inv(int L, int C1, bool u8out, const int16_t *llin, const int1
                       void *out, const StageParams &P, hipStream_t s);
 hipError_t launch_ctr(const uint8_t *in, uint8_t *out, uint64_t nbytes, const AesKey &key,
                       uint64_t first_block, hipStream_t s);
-int inv_waves_per_cu(int L, int C1, bool u8out);
-int inv_split_waves_per_cu(int L, int C1, bool all_fast);
-bool inv_stage_split_ok(const StageParams &P);
-bool inv_stage_all_fast(const StageParams &P, int L, int C1);
 
 static constexpr AesTables kHostTables = make_aes_tables();
 
@@ -126,49 +121,6 @@ void level_offsets(const Geometry &g, uint32_t l, int64_t *hl, int64_t *lh, int6
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-// Wavefronts the current device keeps resident at once for the inverse kernel
-// of a stage: compute units x resident wavefronts per CU (queried once per device
-// and kernel variant; falls back to 256 x 16 if the queries fail).  split:
-// 0 for the one-launch kernels, 1 / 2 for the split restore's packed kernel
-// with every wavefront FAST / not.
-int64_t device_slots(int L, int C1, bool bytes, int split = 0) {
-  constexpr int kDev = 16, kVar = 5 * 3 * 2 * 2;
-  static std::atomic<int> cache[kDev][kVar];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDev) dev = -1;
-  const int var = (L * 3 + split) * 4 + (C1 == 16 ? 2 : 0) + (bytes ? 1 : 0);
-  if (dev >= 0) {
-    const int v = cache[dev][var].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-  }
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess)
-    cus = 0;
-  const int per_cu = split ? inv_split_waves_per_cu(L, C1, split == 1)
-                           : inv_waves_per_cu(L, C1, bytes);
-  const int slots = (cus > 0 && per_cu > 0) ? cus * per_cu : 256 * 16;
-  if (dev >= 0) cache[dev][var].store(slots, std::memory_order_relaxed);
-  return slots;
-}
-
-// SIMDs of the current device (4 per compute unit), cached per device.
-int64_t device_simds() {
-  constexpr int kDev = 16;
-  static std::atomic<int> cache[kDev];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDev) dev = -1;
-  if (dev >= 0) {
-    const int v = cache[dev].load(std::memory_order_relaxed);
-    if (v > 0) return v;
-  }
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev < 0 ? 0 : dev) != hipSuccess)
-    cus = 0;
-  const int simds = cus > 0 ? 4 * cus : 1024;
-  if (dev >= 0) cache[dev].store(simds, std::memory_order_relaxed);
-  return simds;
-}
-
 // Rows of a forward segment.  A segment recomputes 2^(L+1) + 2^L - 3 rows, so
 // taller is less work, but every wavefront is one serial stream: a launch of
 // its own wants about 940 of them (at one level, where the cipher counts
@@ -187,6 +139,22 @@ int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells, bool alone) {
   return std::min(rows, fwd_max_rows(L, C1));
 }
 
+// Rows of an inverse segment: the least that make no more than two wavefronts
+// for each of the 1024 SIMDs (four where the row's end cuts a lane's columns:
+// those wavefronts take 2.5 times as long a row), up to 32 rows (at four
+// levels 48).  Measured, us: 16 MiB of width 4096 at three levels 24 rows
+// 18.6, 16: 19.9, 32: 21.1; 12 MB of width 3001 at two levels 8 rows 24.6,
+// 16: 26.8, 32: 32.2; 256 MiB at three levels 32 rows 158, 24: 163, 48: 158,
+// 64: 160; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
+int inv_seg_rows(int L, int C1, int n_win, int W, int H, bool alone) {
+  const int unit = 1 << L, most = std::min(L == 4 ? 48 : 32, inv_max_rows(L, C1));
+  if (!alone) return most;
+  const int64_t waves = W % C1 ? 4096 : 2048;
+  int rows = unit;
+  while (rows < most && int64_t(n_win) * ((H + rows - 1) / rows) > waves) rows += unit;
+  return std::min(rows, most);
+}
+
 // Fill stage s's parameters.  forward selects the halo shape of the direction;
 // alone: the stage runs as its own launch (not as one item of a batch that
 // shares the device).
@@ -196,12 +164,13 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   const int lv0 = kMaxFused * s;  // global level of the stage input
   const int L = int(std::min<uint32_t>(kMaxFused, g.levels - lv0));
   // Default columns per lane: 8, but 16 (the per-row work spread over twice
-  // the columns) for an inverse stage of at least 64 Mi elements (256 MiB at
-  // three levels 248 -> 227 us), and a forward of three levels and 128 Mi
-  // (176 against 181 us at 256 MiB; 46.2 against 46.9 at 64 MiB, and one and
-  // two levels are as fast at 8: 228, 168 against 227, 169).
+  // the columns) for a forward of three levels and 128 Mi elements (176
+  // against 181 us at 256 MiB; 46.2 against 46.9 at 64 MiB, and one and two
+  // levels are as fast at 8: 228, 168 against 227, 169).  The inverse at 16
+  // is slower at all sizes (256 MiB at one, two and three levels 268, 166,
+  // 161 against 253, 162, 158 us).  Four levels need 16 columns.
   const uint64_t cells = uint64_t(g.h[lv0]) * g.w[lv0];
-  const bool wide = forward ? L == 3 && cells >= (uint64_t(1) << 27) : cells >= (uint64_t(1) << 26);
+  const bool wide = forward && L == 3 && cells >= (uint64_t(1) << 27);
   int C1 = (launch && launch->lane_cols) ? int(launch->lane_cols) : (wide ? 16 : 8);
   if (C1 != 8 && C1 != 16) return DWTFRAG_EINVAL;
   if (L == 4) C1 = 16;
@@ -226,71 +195,35 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
     P->n_win = 1;
   } else {
     P->own_w = span - hl - hr;
-    // A forward window owns whole 128-byte lines of its level-1 band rows:
-    // lines that two windows share are written in parts (256 MiB at three
-    // levels: 448 of 512 columns 185 us, 496 columns 251 us).
-    if (forward) P->own_w = P->own_w / 128 * 128;
+    // A window owns whole lines of what it writes: lines that two windows
+    // share are written in parts.  Forward: 128 bytes of its level-1 band rows
+    // (256 MiB at three levels: 448 of 512 columns 185 us, 496 columns 251
+    // us).  Inverse: 64 bytes of an output row (448 columns 165 us, 488: 172,
+    // 384: 170, each before rows loaded ahead were clamped), but at one level, where the cipher of the columns that
+    // windows share costs more, all it can (496 columns 253 us, 448: 276).
+    const int whole = forward ? 128 : L == 1 ? 1 : 64;
+    P->own_w = P->own_w / whole * whole;
     P->n_win = (P->W + P->own_w - 1) / P->own_w;
   }
   P->halo_l = hl;
-  // The inverse's last window: when the row is a whole number of lane
-  // vectors, its lanes are placed to end at the row's end (a larger left
-  // halo), so every lane reads whole vectors inside every band row.  The
-  // forward keeps the plain placement.
-  P->last_base = P->n_win > 1 ? (P->n_win - 1) * P->own_w - hl : 0;
-  if (!forward && P->n_win > 1 && P->W % C1 == 0 && P->W >= span)
-    P->last_base = std::min(P->last_base, P->W - span);
   P->halo_t = forward ? (1 << (L + 1)) : (1 << L);
   P->halo_b = 1 << L;
   const int unit = 1 << L;
   P->unit_rows = unit;
   P->units = (P->H + unit - 1) / unit;
-  int64_t n_seg;
+  int rows = forward ? fwd_seg_rows(L, C1, P->n_win, P->H, cells, alone)
+                     : inv_seg_rows(L, C1, P->n_win, P->W, P->H, alone);
   if (launch && launch->seg_rows) {
-    int own_h = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
-    if (forward) own_h = std::min(own_h, fwd_max_rows(L, C1));
-    n_seg = (int64_t(P->H) + own_h - 1) / own_h;
-  } else if (forward) {
-    const int rows = fwd_seg_rows(L, C1, P->n_win, P->H, cells, alone);
-    n_seg = (int64_t(P->H) + rows - 1) / rows;
-  } else {
-    // one round of resident wavefronts: as many segments as fill the device
-    // once, each at least two units long (halo work stays below the owned).
-    // A launch of its own whose grid stays within one wavefront per SIMD
-    // even at one unit per segment takes one unit per segment: the extra
-    // halo rows run on otherwise idle SIMDs and each stream is shorter.
-    // A restore's byte stage that runs as the split pair is filled to the
-    // packed kernel's own residency (three wavefronts per SIMD at 16
-    // columns, where the one-launch kernel holds two: 256 MiB at three
-    // levels, restore 210 -> 195 us), and planned again with the one-launch
-    // kernel's when the finished plan turns out not to run split.
-    const int min_units = (alone && int64_t(P->units) * P->n_win <= device_simds()) ? 1 : 2;
-    const auto segments = [&](int split) {
-      const int64_t slots = device_slots(L, C1, s == 0, split);
-      const int64_t k = std::max<int64_t>(1, slots / P->n_win);
-      return std::min<int64_t>(k, std::max(1, P->units / min_units));
-    };
-    const int split = (alone && !forward && s == 0 && P->n_valid >= (int64_t(1) << 24))
-                          ? (inv_stage_all_fast(*P, L, C1) ? 1 : 2) : 0;
-    n_seg = segments(split);
-    if (split) {
-      P->n_seg = int32_t(std::min<int64_t>(n_seg, P->units));
-      if (!inv_stage_split_ok(*P)) n_seg = segments(0);
-    }
+    rows = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
+    rows = std::min(rows, forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1));
   }
+  const int64_t n_seg = (int64_t(P->H) + rows - 1) / rows;
   P->n_seg = int32_t(std::min<int64_t>(std::max<int64_t>(n_seg, 1), P->units));
   const int64_t waves = int64_t(P->n_win) * P->n_seg;
   if (waves > (int64_t(1) << 30)) return DWTFRAG_ERANGE;
   P->n_waves = int32_t(waves);
   const bool last = (s == g.stages - 1);
   P->use_aes = last ? 1 : 0;
-  // keystream ring: LL columns per wavefront (forward: owned, inverse: lanes)
-  const int ll_cols = forward ? std::min<int>(P->wdim[L], (P->own_w >> L) + 1)
-                              : std::min<int>(P->wdim[L], span >> L);
-  P->ks_blocks = (2 * ll_cols + 30) / 16;
-  P->ks_rows = std::max(1, 64 / P->ks_blocks);
-  if (P->ks_rows * P->ks_blocks > kRingBlocks) P->ks_rows = kRingBlocks / P->ks_blocks;
-  if (P->ks_rows < 1) return DWTFRAG_ERANGE;
   P->key = key;
   *L_out = L;
   *C1_out = C1;

@@ -99,15 +99,14 @@ int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count, const dwtfra
       delete b;
       return DWTFRAG_EINVAL;
     }
-    const dwtfrag_launch ln{tl && tl->seg_rows ? tl->seg_rows : 128u, uint32_t(kBatchCols)};
-    const dwtfrag_launch lf{tl ? tl->seg_rows : 0u, uint32_t(kBatchCols)};
+    const dwtfrag_launch ln{tl ? tl->seg_rows : 0u, uint32_t(kBatchCols)};
     AesKey key;
     expand_key(src.key, src.nonce, &key);
     BatchItem &bi = b->items[i];
     std::memset(&bi, 0, sizeof(bi));
     int Lf = 0, Cf = 0, Li = 0, Ci = 0;
     uint64_t priv_bytes = 0;
-    int rc = plan_single_stage(src.n, src.width, src.levels, true, &lf, key, &bi.fwd, &Lf, &Cf, &priv_bytes);
+    int rc = plan_single_stage(src.n, src.width, src.levels, true, &ln, key, &bi.fwd, &Lf, &Cf, &priv_bytes);
     if (rc == DWTFRAG_OK)
       rc = plan_single_stage(src.n, src.width, src.levels, false, &ln, key, &bi.inv, &Li, &Ci, &priv_bytes);
     if (rc != DWTFRAG_OK) {

@@ -12,8 +12,6 @@ namespace dwtfrag {
 constexpr int kMaxFused = 4;
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlockThreads = 64 * kWavesPerBlock;
-// Keystream ring per wavefront: up to 96 AES blocks of 16 bytes.
-constexpr int kRingBlocks = 96;
 
 // ----------------------------------------------------------------- AES-128 --
 // FIPS-197 S-box: multiplicative inverse in GF(2^8) mod x^8+x^4+x^3+x+1, then
@@ -203,11 +201,9 @@ struct StageParams {
   int32_t unit_rows, units;   // 2^L, ceil(H / 2^L)
   int32_t n_seg;              // number of row segments
   int32_t halo_l;             // columns before the owned range (multiple of lane_cols)
-  int32_t last_base;          // first column of the last window's lanes (n_win > 1)
   int32_t halo_t, halo_b;     // rows streamed before / after the owned range
   int32_t n_waves;
   int32_t use_aes;            // LL output / input goes through AES-CTR
-  int32_t ks_rows, ks_blocks; // keystream ring: rows per refill, blocks per row
   AesKey key;
 };
 
@@ -220,23 +216,22 @@ constexpr int fwd_max_rows(int L, int C1) { return fwd_ll_rows(L, C1) << L; }
 constexpr int fwd_ks_words(int L, int C1) {
   return fwd_ll_rows(L, C1) * (64 * C1 / (8 << L) + 2) * 4;
 }
-// Wavefronts per workgroup of a forward launch: one where the whole grid is
+// Inverse kernel: the same limit; its keystream takes the window's lanes, one
+// row above and one below the segment's, and a block that lanes past the
+// row's end may read.
+constexpr int inv_max_rows(int L, int C1) { return fwd_max_rows(L, C1); }
+constexpr int inv_ks_words(int L, int C1) {
+  return ((fwd_ll_rows(L, C1) + 2) * (64 * C1 / (8 << L) + 2) + 1) * 4;
+}
+// Wavefronts per workgroup of a launch: one where the whole grid is
 // about a wavefront per compute unit (each then has an LDS of its own for
 // the AES lookups), else four.
-constexpr int fwd_block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBlock; }
+constexpr int block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBlock; }
 
 // A stage's parameters as the kernels take them (SP below): a kernel argument,
 // or an entry of a batch's item table, read through the constant address
 // space so that it comes by scalar loads.
 using ConstStage = const __attribute__((address_space(4))) StageParams;
-
-// First level-0 column of window win's lanes: the owned range minus the left
-// halo, from column 0 for the first window; the last window's lanes may start
-// further left (last_base) so that they end inside the row.
-template <class SP> __device__ __forceinline__ int window_base(SP &P, int win) {
-  if (win == 0) return 0;
-  return win == P.n_win - 1 ? P.last_base : win * P.own_w - P.halo_l;
-}
 
 // First level-0 row of segment s (s == n_seg gives units * unit_rows).
 template <class SP> __device__ __forceinline__ int seg_start(SP &P, int s) {
@@ -255,6 +250,12 @@ template <class T> __device__ __forceinline__ gptr<T> glob(T *p) { return (gptr<
 // read from any address space).
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// n dwords as one vector.
+template <int n> using Vec = uint32_t __attribute__((ext_vector_type(n)));
+// The same at any byte address: rows of a width that is no multiple of the
+// vector are read unaligned.
+typedef u32x2 u32x2_u __attribute__((aligned(1)));
+typedef u32x4 u32x4_u __attribute__((aligned(1)));
 
 // A pointer that is the same in every lane, in scalar registers.
 template <class T> __device__ __forceinline__ T *uniform_ptr(T *p) {

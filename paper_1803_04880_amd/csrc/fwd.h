@@ -36,11 +36,6 @@
 
 namespace dwtfrag {
 
-// Vectors at any byte address: rows of a width that is no multiple of the
-// vector are read and written unaligned.
-typedef u32x2 u32x2_u __attribute__((aligned(1)));
-typedef u32x4 u32x4_u __attribute__((aligned(1)));
-
 // A wavefront's rectangle and window.
 struct FwdRect {
   int win, seg;

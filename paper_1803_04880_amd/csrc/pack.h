@@ -155,6 +155,27 @@ __device__ __forceinline__ void hinv_pk(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[P
   }
 }
 
+// The same for a window whose lanes a row's ends cannot cut (see
+// hfwd_pk_lanes).
+template <int M>
+__device__ __forceinline__ void hinv_pk_lanes(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[Pk<M>::P],
+                                              bool redge) {
+  constexpr int P = Pk<M>::P;
+  const uint32_t prv = uint32_t(from_prev_lane(int(O[P - 1]), int(M >= 2 ? O[0] << 16 : O[0])));
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const uint32_t dl = (j > 0) ? align16(O[j], O[j - 1]) : (M >= 2 ? align16(O[0], prv) : prv);
+    E[j] = pk_sub(E[j], pk_sra(pk_add(pk_add(dl, O[j]), 0x00020002u), 2));
+  }
+  uint32_t nxt = uint32_t(from_next_lane(int(E[0])));
+  nxt = redge ? (M >= 2 ? E[P - 1] >> 16 : E[0]) : nxt;
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const uint32_t en = (j + 1 < P) ? align16(E[j + 1], E[j]) : (M >= 2 ? align16(nxt, E[j]) : nxt);
+    O[j] = pk_add(O[j], pk_sra(pk_add(E[j], en), 1));
+  }
+}
+
 template <int M>
 __device__ __forceinline__ void hinv_pk_any(uint32_t (&E)[Pk<M>::P], uint32_t (&O)[Pk<M>::P], int j0,
                                             int N, bool edge) {

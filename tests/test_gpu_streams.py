@@ -19,7 +19,7 @@ if not gpu_available():
 import torch  # noqa: E402
 
 import paper_1803_04880_amd as dwtfrag  # noqa: E402
-from oracle import fragment  # noqa: E402
+from oracle import aes128, fragment  # noqa: E402
 
 DEV = "cuda:0"
 
@@ -79,3 +79,52 @@ def test_deep_stages(levels):
     """int16 stages behind the byte stage, at odd and even inner sizes."""
     for width, height in ((2064, 530), (1037, 611)):
         _check(width * height - 11, width, levels, None)
+
+
+@pytest.mark.parametrize("levels,cols", [(1, 8), (2, 8), (3, 8), (1, 16), (2, 16), (3, 16), (4, 16)])
+def test_restore_window_edges(levels, cols):
+    """Rows ending around the columns that an inverse window owns: at one
+    level all but the halos, else whole 64-column pieces."""
+    own = 64 * cols - 16 if cols == 8 else 64 * cols - 32
+    own = own if levels == 1 else own // 64 * 64
+    for i, width in enumerate([own - 1, own, own + 1, own + cols - 1, own + cols, 2 * own, 2 * own + 3]):
+        _check((19 + 3 * i) * width - (i % 3) * (width // 3), width, levels, (0, cols))
+
+
+@pytest.mark.parametrize("width", [1, 2, 5, 19, 77, 501, 1001])
+@pytest.mark.parametrize("levels", [1, 2, 3, 4])
+def test_values_outside_the_packed_range_at_row_ends(width, levels):
+    """Values outside [-4096, 4095] in the last column of a band row, where
+    the row's end cuts a lane and the next row's values follow in the
+    fragment, and in the fragment's last values: the exact inverse, from each
+    alone and from all."""
+    height = 45
+    n = height * width
+    rng = np.random.default_rng([width, levels])
+    key, nonce = rng.bytes(16), rng.bytes(16)
+    g = fragment.geometry(n, width, levels)
+    shapes = g["shapes"]
+    ends = []                      # the last value of some row of each band
+    off = 0
+    for l in range(levels, 0, -1):
+        (h0, w0), (h1, w1) = shapes[l - 1], shapes[l]
+        for rows, cols in ((h1, w0 - w1), (h0 - h1, w1), (h0 - h1, w0 - w1)):
+            if rows * cols:
+                ends.append(off + (rows // 2 + 1) * cols - 1 if rows > 1 else off + cols - 1)
+            off += rows * cols
+    base_ll = rng.integers(-200, 600, g["priv_bytes"] // 2).astype("<i2")
+    base_pub = rng.integers(-300, 301, g["pub_bytes"] // 2).astype("<i2")
+    last = base_pub.size - 1
+    for where in [[e] for e in ends[:3]] + [[last], ends]:
+        ll, pub = base_ll.copy(), base_pub.copy()
+        for e in where:
+            if 0 <= e < pub.size:
+                pub[e] = 20000
+        if len(where) > 1:
+            ll[-1] = -20000
+        priv = aes128.ctr_xor(key, nonce, ll.tobytes()).tobytes()
+        print(f"width={width} levels={levels} outside at {where}", flush=True)
+        tp = torch.from_numpy(np.frombuffer(priv, np.uint8).copy()).to(DEV)
+        tq = torch.from_numpy(pub).to(DEV)
+        got = dwtfrag.restore(tp, tq, n, width, levels, key, nonce).cpu().numpy().tobytes()
+        assert got == fragment.restore(priv, pub.tobytes(), n, width, levels, key, nonce)
