@@ -936,12 +936,16 @@ hipError_t learned_restore_levels(const int16_t *ll_in, const LearnedLevel *lv, 
 
 // ------------------------------------------------------------ trainer --
 
+constexpr int kAdamThreads = 1024;
+
 // Exponent k in [-30, 30]: the largest with maxabs * 2^k < 127.5 (30 for 0).
 // Products with powers of two are exact, so this matches any exact reference.
 __device__ int pow2_exponent(float maxabs) {
-  int k = 30;
-  while (k > -30 && maxabs * ldexpf(1.0f, k) >= 127.5f) --k;
-  return k;
+  if (!(maxabs > 0.0f)) return 30;
+  if (isinf(maxabs)) return -30;
+  int e;
+  const float f = frexpf(maxabs, &e);  // f 2^e, f in [1/2, 1)
+  return min(max(f * 128.0f < 127.5f ? 7 - e : 6 - e, -30), 30);
 }
 
 __device__ float block_max_abs(float v, float *red) {
@@ -958,9 +962,9 @@ __device__ float block_max_abs(float v, float *red) {
 }
 
 // Integer network from the float parameters: power-of-two scales, round half
-// to even, clamps to the parameter ranges.  Run by one 256-thread block.
+// to even, clamps to the parameter ranges.  Run by one block (all its threads).
 __device__ void quantize_block(dwtfrag_trainer *st) {
-  __shared__ float red[8];
+  __shared__ float red[kAdamThreads / 64];
   const int t = int(threadIdx.x);
   const float th = t < kParams ? st->theta[t] : 0.0f;
   const float m1 = block_max_abs(t < 128 ? th : 0.0f, red);
@@ -1008,109 +1012,193 @@ __device__ __forceinline__ int64_t wave_sum(int64_t v) {
   return v;
 }
 
+// Element r of the 16 sums over a 16-lane row, v[i] summed over its lanes:
+// lane c of the row gets the total of v[c].  Each exchange halves the
+// elements a lane keeps; mirroring pairs lanes that differ in the bit that
+// chooses (and in lower bits, over which later exchanges sum).
+template <int ctrl> __device__ __forceinline__ int from_dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int row_scatter_sum(const int (&v)[16], int c) {
+  constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowMirror = 0x140, kHalfMirror = 0x141;
+  int a[8], b[4], d[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int keep = (c & 8) ? v[8 + i] : v[i], give = (c & 8) ? v[i] : v[8 + i];
+    a[i] = keep + from_dpp<kRowMirror>(give);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int keep = (c & 4) ? a[4 + i] : a[i], give = (c & 4) ? a[i] : a[4 + i];
+    b[i] = keep + from_dpp<kHalfMirror>(give);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int keep = (c & 2) ? b[2 + i] : b[i], give = (c & 2) ? b[i] : b[2 + i];
+    d[i] = keep + from_dpp<kQuadXor2>(give);
+  }
+  const int keep = (c & 1) ? d[1] : d[0], give = (c & 1) ? d[0] : d[1];
+  return keep + from_dpp<kQuadXor1>(give);
+}
+
 // Stage 1: per-block integer sums over the pairs, for the current network:
 //   S_w1[k][j] = sum sg [pre_k > 0] c_j,   S_b1[k] = sum sg [pre_k > 0],
 //   S_w2[k] = sum sg h_k,   S_b2 = sum sg,   S_loss = sum |acc - t 2^shift|,
 // with acc = W2 . h + b2 (the network output times 2^shift) and
 // sg = sign(acc - t 2^shift).
-__global__ __launch_bounds__(256) void grad_partial_kernel(const uint2 *__restrict__ ctx,
-                                                           const int32_t *__restrict__ tgt,
-                                                           int64_t count, int64_t stride,
-                                                           const dwtfrag_trainer *__restrict__ st,
-                                                           int64_t *__restrict__ partial) {
-  __shared__ int64_t red[4][kSums];
-  Net net;
-  {
-    const dwtfrag_predictor &q = st->net;
-    net = Net{};
-    for (int k = 0; k < kHidden; ++k) {
-      net.w1[k][0] = uint32_t(uint8_t(q.w1[k][0])) | (uint32_t(uint8_t(q.w1[k][1])) << 8) |
-                     (uint32_t(uint8_t(q.w1[k][2])) << 16) | (uint32_t(uint8_t(q.w1[k][3])) << 24);
-      net.w1[k][1] = uint32_t(uint8_t(q.w1[k][4])) | (uint32_t(uint8_t(q.w1[k][5])) << 8) |
-                     (uint32_t(uint8_t(q.w1[k][6])) << 16) | (uint32_t(uint8_t(q.w1[k][7])) << 24);
-      net.b1[k] = q.b1[k];
-      net.w2[k] = q.w2[k];
-    }
-    net.b2 = q.b2;
-    net.shift = q.shift;
-  }
-  int32_t s_w1[kHidden][kCtx], s_b1[kHidden];
-  int64_t s_w2[kHidden];
-  int64_t s_b2 = 0, s_loss = 0;
-#pragma unroll
-  for (int k = 0; k < kHidden; ++k) {
-    s_b1[k] = 0;
-    s_w2[k] = 0;
-#pragma unroll
-    for (int j = 0; j < kCtx; ++j) s_w1[k][j] = 0;
-  }
-  const int64_t grid_threads = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < count; p += grid_threads) {
-    const uint2 cw = ctx[p * stride];
-    const int64_t t = tgt[p * stride];
-    int c[kCtx];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      c[j] = int(int8_t(uint8_t(cw.x >> (8 * j))));
-      c[4 + j] = int(int8_t(uint8_t(cw.y >> (8 * j))));
-    }
-    int h[kHidden];
-    int acc = net.b2;
-#pragma unroll
-    for (int k = 0; k < kHidden; ++k) {
-      h[k] = hidden_pre(net.w1[k], net.b1[k], cw.x, cw.y);
-      acc += clamp_i(h[k], 0, 0x7fffff) * ((net.w2[k] << 24) >> 24);
-    }
-    const int64_t r = int64_t(acc) - (t << net.shift);
-    const int sg = (r > 0) - (r < 0);
-    s_loss += r < 0 ? -r : r;
-    s_b2 += sg;
-#pragma unroll
-    for (int k = 0; k < kHidden; ++k) {
-      const int hk = max(h[k], 0);
-      s_w2[k] += sg * hk;
-      const int mk = h[k] > 0 ? sg : 0;
-      s_b1[k] += mk;
-#pragma unroll
-      for (int j = 0; j < kCtx; ++j) s_w1[k][j] += mk * c[j];
-    }
-  }
+//
+// A wavefront takes 64 pairs at a time, lane l the context of pair l.  The
+// sums are a contraction over the pairs, and run on the matrix cores: with
+// the contexts as the first operand (row = pair) a product with W1 gives lane
+// l the pre-activations of hidden unit c = l % 16 for the pairs
+// 16 g + 4 q + r (q = l / 16; g, r = 0 .. 3), and one with the identity the
+// context bytes c of the same pairs.  Both are then in place for the second
+// product over the pairs, masks (hidden unit x pair) times contexts (pair x
+// byte, byte 8 a one for the bias).  The outputs' sums over the 16 hidden
+// units are scattered over the row's lanes, so that lane 16 q + 4 g + r
+// compares pair 16 g + 4 q + r with its target, and the signs come back as
+// two ballots.  All sums are exact integers.
+//
+// What bounds it is the latency of one gather and of the launch: 64 Ki pairs
+// are one step of 1024 wavefronts.  One pair a lane with 162 sums in its
+// registers, reduced over the lanes at the end, took 81 us at 64 Ki pairs,
+// this 5.5.
+constexpr int kGradWaves = 8;
+
+__global__ __launch_bounds__(64 * kGradWaves) void grad_partial_kernel(
+    const uint2 *__restrict__ ctx, const int32_t *__restrict__ tgt, int64_t count, int64_t stride,
+    const dwtfrag_trainer *__restrict__ st, int64_t *__restrict__ partial) {
+  __shared__ int64_t red[kGradWaves][kSums];
   const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63;
+  const int c = lane & 15, q = lane >> 4;
+  const int64_t step = int64_t(gridDim.x) * 64 * kGradWaves;
+  // this lane's pair of 64, and the pair whose output it gets
+  const int64_t first = (int64_t(blockIdx.x) * kGradWaves + wave) * 64;
+  const int mine = 16 * ((lane >> 2) & 3) + 4 * q + (lane & 3);
+  const auto load = [&](int64_t at, uint2 &cw, int32_t &t) {
+    cw = make_uint2(0, 0);
+    t = 0;
+    if (at + lane < count) cw = ctx[(at + lane) * stride];
+    if (at + mine < count) t = tgt[(at + mine) * stride];
+  };
+  uint2 cw;
+  int32_t t;
+  load(first, cw, t);
+
+  const uint8_t *w1 = reinterpret_cast<const uint8_t *>(st->net.w1[c]);
+  uint64_t row = 0;
 #pragma unroll
-  for (int k = 0; k < kHidden; ++k) {
+  for (int j = 0; j < kCtx; ++j) row |= uint64_t(w1[j]) << (8 * j);
+  const int b1 = st->net.b1[c], w2 = st->net.w2[c], b2 = st->net.b2, shift = st->net.shift;
+  const long unit = c < kCtx ? long(uint64_t(1) << (8 * (c & 7))) : 0;
+  const v4i bias = {b1, b1, b1, b1};
+  const int ones = c == kCtx ? 0x01010101 : 0;
+
+  int64_t s_w1[4] = {0, 0, 0, 0};  // hidden units 4 q + r, byte c
+  int64_t s_w2 = 0, s_loss = 0;    // hidden unit c; this lane's pairs
+  int64_t s_b2 = 0;                // (uniform)
+  int64_t at = first;
+  while (at < count) {
+    v4i w1sum = {0, 0, 0, 0};
+    // (32-bit sums of products up to 128 over 64 pairs a step)
+#pragma unroll 1
+    for (int n = 0; n < (1 << 16) && at < count; ++n, at += step) {
+      const long a = long(uint64_t(cw.x) | (uint64_t(cw.y) << 32));
+      const int64_t target = int64_t(t) << shift;
+      const bool live = at + mine < count;
+      load(at + step, cw, t);
+      int h[16], v[16], byte[16];
 #pragma unroll
-    for (int j = 0; j < kCtx; ++j) {
-      const int64_t v = wave_sum(int64_t(s_w1[k][j]));
-      if (lane == 0) red[wave][k * kCtx + j] = v;
+      for (int g = 0; g < 4; ++g) {
+        const v4i d = __builtin_amdgcn_mfma_i32_16x16x32_i8(a, q == g ? long(row) : 0, bias, 0, 0, 0);
+        const v4i e = __builtin_amdgcn_mfma_i32_16x16x32_i8(a, q == g ? unit : 0, v4i{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          h[4 * g + r] = d[r];
+          byte[4 * g + r] = e[r];
+          v[4 * g + r] = clamp_i(d[r], 0, 0x7fffff) * w2;
+        }
+      }
+      int out = row_scatter_sum(v, c) + b2;
+      asm volatile("" : "+v"(out));  // all lanes take part, whatever uses it
+      const int64_t diff = live ? int64_t(out) - target : 0;
+      s_loss += diff < 0 ? -diff : diff;
+      const uint64_t pos = __builtin_amdgcn_ballot_w64(diff > 0), neg = __builtin_amdgcn_ballot_w64(diff < 0);
+      s_b2 += int(__popcll(pos)) - int(__popcll(neg));
+      const int rp = int(pos >> (16 * q)), rn = int(neg >> (16 * q));  // bit 4 g + r: pair 16 g + 4 q + r
+      long mask[2], bytes[2];
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        uint32_t mw[2], cb[2];
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const int g = 2 * half + w;
+          int m[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int i = 4 * g + r;
+            const int sg = ((rp >> i) & 1) - ((rn >> i) & 1);
+            m[r] = h[i] > 0 ? sg : 0;
+            s_w2 += m[r] * h[i];
+          }
+          mw[w] = pack4(m[0], m[1], m[2], m[3]);
+          cb[w] = pack4(byte[4 * g], byte[4 * g + 1], byte[4 * g + 2], byte[4 * g + 3]) | uint32_t(ones);
+        }
+        mask[half] = long(uint64_t(mw[0]) | (uint64_t(mw[1]) << 32));
+        bytes[half] = long(uint64_t(cb[0]) | (uint64_t(cb[1]) << 32));
+      }
+      w1sum = __builtin_amdgcn_mfma_i32_16x16x32_i8(mask[0], bytes[0], w1sum, 0, 0, 0);
+      w1sum = __builtin_amdgcn_mfma_i32_16x16x32_i8(mask[1], bytes[1], w1sum, 0, 0, 0);
     }
-    const int64_t vb = wave_sum(int64_t(s_b1[k]));
-    const int64_t vw = wave_sum(s_w2[k]);
-    if (lane == 0) {
-      red[wave][128 + k] = vb;
-      red[wave][144 + k] = vw;
-    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_w1[r] += w1sum[r];
   }
-  {
-    const int64_t vb = wave_sum(s_b2), vl = wave_sum(s_loss);
-    if (lane == 0) {
-      red[wave][160] = vb;
-      red[wave][161] = vl;
-    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (c < kCtx) red[wave][(4 * q + r) * kCtx + c] = s_w1[r];
+    if (c == kCtx) red[wave][128 + 4 * q + r] = s_w1[r];
+  }
+  s_w2 += __shfl_xor(s_w2, 16);
+  s_w2 += __shfl_xor(s_w2, 32);
+  if (q == 0) red[wave][144 + c] = s_w2;
+  s_loss = wave_sum(s_loss);
+  if (lane == 0) {
+    red[wave][160] = s_b2;
+    red[wave][161] = s_loss;
   }
   __syncthreads();
-  for (int i = int(threadIdx.x); i < kSums; i += blockDim.x)
-    partial[int64_t(blockIdx.x) * kSums + i] = red[0][i] + red[1][i] + red[2][i] + red[3][i];
+  for (int i = int(threadIdx.x); i < kSums; i += 64 * kGradWaves) {
+    int64_t v = 0;
+#pragma unroll
+    for (int w = 0; w < kGradWaves; ++w) v += red[w][i];
+    partial[int64_t(blockIdx.x) * kSums + i] = v;
+  }
 }
 
 // Stage 2 (one block): total sums -> loss and gradient at the fake-quantised
 // point, Adam step on the float parameters, re-quantisation.
-__global__ __launch_bounds__(256) void adam_kernel(dwtfrag_trainer *st, const int64_t *partial,
-                                                   int nblocks, int64_t count, float lr) {
-  __shared__ int64_t S[kSums];
+// The blocks' sums are added by six groups of threads, eight rows in flight
+// each: one thread per sum, one row after the other, took 70 us at 256 blocks
+// of 256 pairs, this 8 at 128 of 512.
+constexpr int kAdamGroups = 6;
+static_assert(kAdamGroups * kSums <= kAdamThreads, "a thread per sum and group");
+
+__global__ __launch_bounds__(kAdamThreads) void adam_kernel(dwtfrag_trainer *st, const int64_t *partial,
+                                                            int nblocks, int64_t count, float lr) {
+  __shared__ int64_t S[kAdamGroups * kSums];
   const int t = int(threadIdx.x);
-  if (t < kSums) {
+  if (t < kAdamGroups * kSums) {
+    const int g = t / kSums, i = t - g * kSums;
     int64_t v = 0;
-    for (int b = 0; b < nblocks; ++b) v += partial[int64_t(b) * kSums + t];
+#pragma unroll 8
+    for (int b = g; b < nblocks; b += kAdamGroups) v += partial[int64_t(b) * kSums + i];
+    S[t] = v;
+  }
+  __syncthreads();
+  if (t < kSums) {
+    int64_t v = S[t];
+#pragma unroll
+    for (int g = 1; g < kAdamGroups; ++g) v += S[g * kSums + t];
     S[t] = v;
   }
   __syncthreads();
@@ -1358,14 +1446,15 @@ int dwtfrag_trainer_step(dwtfrag_trainer *state, const int8_t *ctx, const int32_
       (count - 1) > ((uint64_t(1) << 62) / stride))
     return DWTFRAG_ERANGE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const uint64_t want = (count + 255) / 256;
+  constexpr uint64_t kPerBlock = 64 * kGradWaves;
+  const uint64_t want = (count + kPerBlock - 1) / kPerBlock;
   const int blocks = int(want < uint64_t(kGradBlocks) ? want : uint64_t(kGradBlocks));
   int64_t *partial = static_cast<int64_t *>(workspace);
-  hipLaunchKernelGGL(grad_partial_kernel, dim3(blocks), dim3(256), 0, st,
+  hipLaunchKernelGGL(grad_partial_kernel, dim3(blocks), dim3(unsigned(kPerBlock)), 0, st,
                      reinterpret_cast<const uint2 *>(ctx), target, int64_t(count), int64_t(stride),
                      state, partial);
   if (hipGetLastError() != hipSuccess) return DWTFRAG_EDEVICE;
-  hipLaunchKernelGGL(adam_kernel, dim3(1), dim3(256), 0, st, state, partial, blocks,
+  hipLaunchKernelGGL(adam_kernel, dim3(1), dim3(kAdamThreads), 0, st, state, partial, blocks,
                      int64_t(count), lr);
   return hipGetLastError() == hipSuccess ? DWTFRAG_OK : DWTFRAG_EDEVICE;
 }

@@ -240,3 +240,41 @@ def test_gpu_trained_network_lowers_detail_entropy():
     _say(f"detail entropy plain {e_plain:.4f} learned {e_learned:.4f} bits")
     assert e_learned < e_plain
     assert _restore(priv, pub, img.size, 512, 3, key, nonce, net) == img.tobytes()
+
+
+@pytest.mark.parametrize("count,stride", [(1, 1), (63, 2), (64, 1), (65, 3), (511, 1), (512, 7), (513, 1),
+                                          (4097, 2), (262143, 1), (262145, 1), (600001, 1)])
+@pytest.mark.parametrize("scale", [1.0, 300.0])
+def test_trainer_sums_are_exact(count, stride, scale):
+    """The gradient is the integer sums over the pairs, scaled once in
+    float64 and rounded to float32: equal to numpy's int64 sums at the edges
+    of a wavefront's 64 pairs, a workgroup's 512 and the whole grid's."""
+    rng = np.random.default_rng([count, stride])
+    total = (count - 1) * stride + 1
+    c = rng.integers(-128, 128, (total, 8)).astype(np.int8)
+    t = rng.integers(-600, 601, total).astype(np.int32)
+    tr = GL.Trainer((synth.mlp_init(OL.N_PARAMS, 73) * scale).astype(np.float32), DEV)
+    st = tr.read()
+    net, k1, k2 = st.net, int(st.k1), int(st.k2)
+    w1 = np.array([[net.w1[k][j] for j in range(8)] for k in range(16)], np.int64)
+    w2 = np.array(list(net.w2), np.int64)
+    b1 = np.array(list(net.b1), np.int64)
+    cs, ts = c[::stride].astype(np.int64), t[::stride].astype(np.int64)
+    assert len(ts) == count
+    pre = cs @ w1.T + b1
+    h = np.maximum(pre, 0)
+    r = h @ w2 + int(net.b2) - (ts << int(net.shift))
+    sg = np.sign(r)
+    m = (pre > 0) * sg[:, None]
+    inv_n, f = 1.0 / float(count), 2.0 ** -k2
+    want = np.empty(161)
+    want[:128] = np.repeat(w2, 8).astype(float) * (m.T @ cs).reshape(-1).astype(float) * f * inv_n
+    want[128:144] = w2.astype(float) * m.sum(0).astype(float) * f * inv_n
+    want[144:160] = (sg @ h).astype(float) * 2.0 ** -k1 * inv_n
+    want[160] = float(sg.sum()) * inv_n
+    loss = np.float32(float(np.abs(r).sum()) * 2.0 ** -int(net.shift) * inv_n)
+    print(f"count={count} stride={stride} scale={scale}", flush=True)
+    tr.step(torch.from_numpy(c).to(DEV), torch.from_numpy(t).to(DEV), 0.01, 0, stride)
+    st = tr.read()
+    assert np.array_equal(np.frombuffer(bytes(st.grad), np.float32), want.astype(np.float32))
+    assert np.float32(st.loss) == loss
