@@ -445,19 +445,19 @@ static_assert(kLvW == 128, "the row passes give each lane two columns of a 128-c
 // Tile loads: each thread keeps eight global loads in flight, then writes
 // them to LDS (load(idx) reads element idx of the tile, store(idx, v)
 // places it).
-template <int TOTAL, class Load, class Store>
+template <int TOTAL, int NW, class Load, class Store>
 __device__ __forceinline__ void tile_load(const Load &load, const Store &store) {
-  constexpr int kU = 8;
-  for (int base = 0; base < TOTAL; base += 256 * kU) {
+  constexpr int kU = 8, kT = 64 * NW;
+  for (int base = 0; base < TOTAL; base += kT * kU) {
     int v[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int idx = base + u * 256 + int(threadIdx.x);
+      const int idx = base + u * kT + int(threadIdx.x);
       v[u] = idx < TOTAL ? load(idx) : 0;
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int idx = base + u * 256 + int(threadIdx.x);
+      const int idx = base + u * kT + int(threadIdx.x);
       if (idx < TOTAL) store(idx, v[u]);
     }
   }
@@ -561,8 +561,8 @@ __device__ __forceinline__ void load_context(const T *at, int stride, int (&e)[k
   for (int j = 0; j < kCtx; ++j) e[j] = at[2 * j * stride];
 }
 
-template <class Src>
-__global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, const Net net, int H,
+template <class Src, int NW>
+__global__ __launch_bounds__(64 * NW) void lfwd_level_kernel(Src src, LvBands out, const Net net, int H,
                                                          int W, int tiles_x) {
   __shared__ int16_t X[(kFwdH + 16) * kLvPitch];
   __shared__ uint32_t s_net[64];
@@ -580,26 +580,26 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
   // every sample of the tile singly instead
   bool miss = !src.vec;
   if (src.vec) {
-    const int slot = tid % 36, grp = tid / 36;  // 7 groups; threads 252 .. 255 idle
-    constexpr int kU = 4;
-    for (int t0 = 0; t0 < kRows; t0 += 7 * kU) {
+    const int slot = tid % 36, grp = tid / 36;  // whole groups; the last threads idle
+    constexpr int kG = 64 * NW / 36, kU = NW > 4 ? 2 : 4;
+    for (int t0 = 0; t0 < kRows; t0 += kG * kU) {
       decltype(src.quad(0, 0, 0, &miss)) v[kU];
       bool ok[kU];
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int t = min(t0 + grp + 7 * u, kRows - 1);
+        const int t = min(t0 + grp + kG * u, kRows - 1);
         v[u] = src.quad(mirror_pos(r0 - 8 + local_row(t), H), c0 - 8 + 4 * slot, W, &ok[u]);
-        ok[u] = ok[u] && grp < 7 && t0 + grp + 7 * u < kRows;
-        miss |= grp < 7 && t0 + grp + 7 * u < kRows && !ok[u];
+        ok[u] = ok[u] && grp < kG && t0 + grp + kG * u < kRows;
+        miss |= grp < kG && t0 + grp + kG * u < kRows && !ok[u];
       }
 #pragma unroll
       for (int u = 0; u < kU; ++u)
         if (ok[u])
-          *reinterpret_cast<uint2 *>(X + local_row(t0 + grp + 7 * u) * P + 4 * slot) = Src::widen(v[u]);
+          *reinterpret_cast<uint2 *>(X + local_row(t0 + grp + kG * u) * P + 4 * slot) = Src::widen(v[u]);
     }
   }
   if (__syncthreads_or(miss)) {
-    tile_load<kRows * kCols>(
+    tile_load<kRows * kCols, NW>(
         [&](int idx) {
           const int t = idx / kCols, q = idx - t * kCols;
           return src(mirror_pos(r0 - 8 + local_row(t), H), mirror_pos(c0 - 8 + q, W));
@@ -619,13 +619,13 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
   {
     const int q = 9 + 2 * lane;
     const bool col_ok = c0 + 1 + 2 * lane < W;
-    for (int t = wave; t < kRows; t += 4) {
+    for (int t = wave; t < kRows; t += NW) {
       int16_t *row = X + local_row(t) * P;
       int base;
       const int corr = correction_packed(mn, context16(row + q - 7, 1, &base));
       if (col_ok) row[q] = int16_t(row[q] - base - corr);
     }
-    for (int b = (wave + 4 - kRows % 4) % 4; b < (kRows + 63) / 64; b += 4) {
+    for (int b = (wave + NW - kRows % NW) % NW; b < (kRows + 63) / 64; b += NW) {
       const int t = b * 64 + lane;
       const bool in = t < kRows;
       int16_t *at = X + local_row(in ? t : 0) * P + 7;
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
   __syncthreads();
   // row pass, update at the owned even columns (q = 8 + 2 lane)
   if (W > 1) {
-    for (int t = wave; t < kRows; t += 4) {
+    for (int t = wave; t < kRows; t += NW) {
       const int k = local_row(t), q = 8 + 2 * lane, c = c0 + 2 * lane;
       if (c < W) {
         int16_t *row = X + k * P;
@@ -650,7 +650,7 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
   __syncthreads();
   // column pass, predict at the odd rows k = 7 (r0 - 1), 9, .., kFwdH+7 of
   // the owned columns, 64 columns per batch
-  for (int b = wave; b < (kFwdH / 2 + 1) * 2; b += 4) {
+  for (int b = wave; b < (kFwdH / 2 + 1) * 2; b += NW) {
     const int k = 7 + 2 * (b >> 1), q = 8 + 64 * (b & 1) + lane;
     int base;
     const int corr = correction_packed(mn, context16(X + (k - 7) * P + q, P, &base));
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
   // column pass, update at the owned even rows; each lane stores the band
   // samples of the column pair c0 + 2 lane, +1 (band column c0/2 + lane)
   const int64_t cc = c0 / 2 + lane;
-  for (int m = wave; m < kFwdH / 2; m += 4) {
+  for (int m = wave; m < kFwdH / 2; m += NW) {
     const int k = 8 + 2 * m, r = r0 + 2 * m;
     if (r >= H) break;
     const int64_t rr = r >> 1;
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(256) void lfwd_level_kernel(Src src, LvBands out, c
 // row when t is odd (mirroring keeps parity), so the two parities run as
 // separate passes, each with fixed bands.  Returns whether a quad was
 // missed (the caller then reads the tile singly).
-template <bool ODD, bool LL32>
+template <bool ODD, bool LL32, int NW>
 __device__ __forceinline__ bool inv_quads_parity(const LvCoef &src, int32_t *Z, int r0, int c0, int H,
                                                  int W) {
   constexpr int P = kLvPitch, kR = kInvH + 15;
@@ -703,24 +703,24 @@ __device__ __forceinline__ bool inv_quads_parity(const LvCoef &src, int32_t *Z, 
   // rows of this parity: t = t_first + 2 i
   constexpr int t_first = ODD ? 0 : 1;
   constexpr int n_rows = (kR - t_first + 1) / 2;
-  constexpr int kU = 4;
-  for (int i0 = 0; i0 < n_rows; i0 += 7 * kU) {
+  constexpr int kG = 64 * NW / 36, kU = NW > 4 ? 2 : 4;
+  for (int i0 = 0; i0 < n_rows; i0 += kG * kU) {
     uint32_t a[kU], b[kU];
     uint2 a32[kU];
     bool ok[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int i = min(i0 + grp + 7 * u, n_rows - 1);
+      const int i = min(i0 + grp + kG * u, n_rows - 1);
       src.quad<ODD, LL32>(mirror_pos(r0 - 7 + t_first + 2 * i, H), c0 - 8 + 4 * slot, W, &ok[u], &a[u],
                           &a32[u], &b[u]);
-      const bool mine = grp < 7 && i0 + grp + 7 * u < n_rows;
+      const bool mine = grp < kG && i0 + grp + kG * u < n_rows;
       miss |= mine && !ok[u];
       ok[u] = ok[u] && mine;
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       if (!ok[u]) continue;
-      const int t = t_first + 2 * (i0 + grp + 7 * u);
+      const int t = t_first + 2 * (i0 + grp + kG * u);
       const int b0 = int(b[u] << 16) >> 16, b1 = int(b[u]) >> 16;
       int a0, a1;
       if (!ODD && LL32) {
@@ -736,16 +736,16 @@ __device__ __forceinline__ bool inv_quads_parity(const LvCoef &src, int32_t *Z, 
   return miss;
 }
 
-template <bool LL32>
+template <bool LL32, int NW>
 __device__ __forceinline__ bool inv_tile_quads(const LvCoef &src, int32_t *Z, int r0, int c0, int H,
                                                int W) {
-  const bool m0 = inv_quads_parity<false, LL32>(src, Z, r0, c0, H, W);
-  const bool m1 = inv_quads_parity<true, LL32>(src, Z, r0, c0, H, W);
+  const bool m0 = inv_quads_parity<false, LL32, NW>(src, Z, r0, c0, H, W);
+  const bool m1 = inv_quads_parity<true, LL32, NW>(src, Z, r0, c0, H, W);
   return m0 || m1;
 }
 
-template <class Dst>
-__global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, const Net net, int H,
+template <class Dst, int NW>
+__global__ __launch_bounds__(64 * NW) void linv_level_kernel(LvCoef src, Dst dst, const Net net, int H,
                                                          int W, int tiles_x) {
   __shared__ int32_t Z[(kInvH + 16) * kLvPitch];
   __shared__ uint32_t s_net[64];
@@ -758,10 +758,10 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   // tile loads as in the forward: local rows 1 .. kInvH+15, local columns
   // 0 .. 143 in quads, or every sample singly where a quad is missing
   bool miss = !src.vec;
-  if (src.vec) miss = src.ll32 ? inv_tile_quads<true>(src, Z, r0, c0, H, W)
-                               : inv_tile_quads<false>(src, Z, r0, c0, H, W);
+  if (src.vec) miss = src.ll32 ? inv_tile_quads<true, NW>(src, Z, r0, c0, H, W)
+                               : inv_tile_quads<false, NW>(src, Z, r0, c0, H, W);
   if (__syncthreads_or(miss)) {
-    tile_load<kR * kC>(
+    tile_load<kR * kC, NW>(
         [&](int idx) {
           const int t = idx / kC, q = 1 + idx - t * kC;
           return src(mirror_pos(r0 - 7 + t, H), mirror_pos(c0 - 8 + q, W));
@@ -775,7 +775,7 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   // column pass, undo the update at the even rows k = 2 .. kInvH+14
   if (H > 1) {
     constexpr int kEv = kInvH / 2 + 7;
-    for (int idx = tid; idx < kEv * kC; idx += 256) {
+    for (int idx = tid; idx < kEv * kC; idx += 64 * NW) {
       const int t = idx / kC, k = 2 + 2 * t, q = 1 + idx - t * kC;
       Z[k * P + q] -= (Z[(k - 1) * P + q] + Z[(k + 1) * P + q] + 2) >> 2;
     }
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   // columns per row, then one batch of the last 15 columns of the four rows
   static_assert(kC == 143 && (kInvH / 2) % 4 == 0, "column batches of the inverse tile");
   constexpr int kGroups = kInvH / 2 / 4, kPerGroup = 9;
-  for (int b = wave; b < kGroups * kPerGroup; b += 4) {
+  for (int b = wave; b < kGroups * kPerGroup; b += NW) {
     const int g = b / kPerGroup, j = b - g * kPerGroup;  // wave-uniform
     int k, q;
     bool in = true;
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   // owned rows
   if (W > 1) {
     constexpr int kEv = kLvW / 2 + 7;
-    for (int idx = tid; idx < kInvH * kEv; idx += 256) {
+    for (int idx = tid; idx < kInvH * kEv; idx += 64 * NW) {
       const int t = idx / kEv, k = 8 + t, q = 2 + 2 * (idx - t * kEv);
       int32_t *row = Z + k * P;
       row[q] -= (row[q - 1] + row[q + 1] + 2) >> 2;
@@ -822,7 +822,7 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   __syncthreads();
   // row pass, undo the predict at the owned odd columns (q = 9 + 2 lane) and
   // store the column pair c0 + 2 lane, +1 of each owned row
-  for (int t = wave; t < kInvH; t += 4) {
+  for (int t = wave; t < kInvH; t += NW) {
     const int k = 8 + t, r = r0 + t;
     if (r >= H) break;
     const int q = 9 + 2 * lane, c = c0 + 2 * lane;
@@ -835,13 +835,28 @@ __global__ __launch_bounds__(256) void linv_level_kernel(LvCoef src, Dst dst, co
   }
 }
 
+// Wavefronts a tile.  A level of few tiles leaves the compute units short of
+// wavefronts, and a tile's batches are a serial chain for each of them; the
+// inverse's tiles fill a unit's LDS before its wavefronts.  Kernels of 4096
+// x 4096 at 4 / 8 / 16 wavefronts, us: 4096 tiles forward 75.5 / 76.8 / -,
+// inverse 96.6 / 88.6 / -; 1024 tiles 26.6 / 24.5 / 25.4 and 32.3 / 27.9 /
+// 28.2; 256 tiles 15.6 / 10.9 / 9.3 and 19.6 / 12.5 / 10.3.
+template <int N> struct Waves { static constexpr int value = N; };
+inline int fwd_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : tiles <= 2048 ? 8 : 4; }
+inline int inv_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : 8; }
+
 template <class Src>
 hipError_t fwd_level(Src src, const LvBands &out, const Net &net, int h, int w, hipStream_t s) {
   const int tx = (w + kLvW - 1) / kLvW, ty = (h + kFwdH - 1) / kFwdH;
   const int64_t grid = int64_t(tx) * ty;
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((lfwd_level_kernel<Src>), dim3(unsigned(grid)), dim3(256), 0, s, src, out, net,
-                     h, w, tx);
+  const auto go = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    hipLaunchKernelGGL((lfwd_level_kernel<Src, NW>), dim3(unsigned(grid)), dim3(64 * NW), 0, s, src, out,
+                       net, h, w, tx);
+  };
+  const int waves = fwd_level_waves(grid);
+  waves == 16 ? go(Waves<16>{}) : waves == 8 ? go(Waves<8>{}) : go(Waves<4>{});
   return hipGetLastError();
 }
 
@@ -850,8 +865,12 @@ hipError_t inv_level(const LvCoef &src, Dst dst, const Net &net, int h, int w, h
   const int tx = (w + kLvW - 1) / kLvW, ty = (h + kInvH - 1) / kInvH;
   const int64_t grid = int64_t(tx) * ty;
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((linv_level_kernel<Dst>), dim3(unsigned(grid)), dim3(256), 0, s, src, dst, net,
-                     h, w, tx);
+  const auto go = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    hipLaunchKernelGGL((linv_level_kernel<Dst, NW>), dim3(unsigned(grid)), dim3(64 * NW), 0, s, src, dst,
+                       net, h, w, tx);
+  };
+  inv_level_waves(grid) == 16 ? go(Waves<16>{}) : go(Waves<8>{});
   return hipGetLastError();
 }
 
