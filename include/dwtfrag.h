@@ -188,7 +188,7 @@ typedef struct dwtfrag_batch dwtfrag_batch;  /* opaque host-side plan */
 
 /* Host only: plan `count` items (host array, read before return).  Items of a
  * (width, levels) class listed in `tune` use that entry's rows per tile,
- * others 128-row tiles; batch tiles always have 16 columns per lane (the
+ * others 48 rows (16 at one level); batch tiles always have 16 columns per lane (the
  * entry's lane_cols must be 0, 8 or 16 and is not otherwise used).  *out
  * receives a plan owned by the caller (free it with dwtfrag_batch_destroy).
  * EINVAL for a null or misaligned pointer, levels outside 1..4 or a bad

@@ -131,10 +131,10 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 //   3: 96 rows (8 columns a lane) 46.9 at 64 MiB, 48: 47.7, 16: 56.2; at 16
 //      columns 24 rows 176 at 256 MiB (32: 182, 96: 208);
 //   4: 96 rows 53.7 at 64 MiB (64: 60.9), 64 rows 198 at 256 MiB (96: 214).
-int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells, bool alone) {
+int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells) {
   const bool large = cells >= (uint64_t(1) << 27);
   const int most = L == 1 ? 24 : L == 2 ? (large ? 32 : 16) : L == 3 ? (C1 == 16 ? 24 : 96) : large ? 64 : 96;
-  const int64_t want = alone ? int64_t(n_win) * H / (L == 1 ? 1536 : 940) : most;
+  const int64_t want = int64_t(n_win) * H / (L == 1 ? 1536 : 940);
   const int rows = round_up(int(std::min<int64_t>(std::max<int64_t>(want, 1), most)), 1 << L);
   return std::min(rows, fwd_max_rows(L, C1));
 }
@@ -146,14 +146,19 @@ int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells, bool alone) {
 // 18.6, 16: 19.9, 32: 21.1; 12 MB of width 3001 at two levels 8 rows 24.6,
 // 16: 26.8, 32: 32.2; 256 MiB at three levels 32 rows 158, 24: 163, 48: 158,
 // 64: 160; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
-int inv_seg_rows(int L, int C1, int n_win, int W, int H, bool alone) {
+int inv_seg_rows(int L, int C1, int n_win, int W, int H) {
   const int unit = 1 << L, most = std::min(L == 4 ? 48 : 32, inv_max_rows(L, C1));
-  if (!alone) return most;
   const int64_t waves = W % C1 ? 4096 : 2048;
   int rows = unit;
   while (rows < most && int64_t(n_win) * ((H + rows - 1) / rows) > waves) rows += unit;
   return std::min(rows, most);
 }
+
+// Rows of a batch item's tiles.  The items share the device, so that no tile
+// need be short to fill it: 256 items of 4 KiB to 64 MiB, 1.8 GB, forward /
+// inverse, 24 rows 1458 / 1451 us, 32: 1396 / 1368, 48: 1361 / 1357, 64: 1373
+// / 1388, 96: 1378 / 1417; as single launches' 1562 / 1372.
+constexpr int kBatchRows = 48;
 
 // Fill stage s's parameters.  forward selects the halo shape of the direction;
 // alone: the stage runs as its own launch (not as one item of a batch that
@@ -211,12 +216,12 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   const int unit = 1 << L;
   P->unit_rows = unit;
   P->units = (P->H + unit - 1) / unit;
-  int rows = forward ? fwd_seg_rows(L, C1, P->n_win, P->H, cells, alone)
-                     : inv_seg_rows(L, C1, P->n_win, P->W, P->H, alone);
-  if (launch && launch->seg_rows) {
+  int rows = !alone    ? kBatchRows
+             : forward ? fwd_seg_rows(L, C1, P->n_win, P->H, cells)
+                       : inv_seg_rows(L, C1, P->n_win, P->W, P->H);
+  if (launch && launch->seg_rows)
     rows = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
-    rows = std::min(rows, forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1));
-  }
+  rows = std::min(rows, forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1));
   const int64_t n_seg = (int64_t(P->H) + rows - 1) / rows;
   P->n_seg = int32_t(std::min<int64_t>(std::max<int64_t>(n_seg, 1), P->units));
   const int64_t waves = int64_t(P->n_win) * P->n_seg;

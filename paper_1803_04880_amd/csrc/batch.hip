@@ -92,7 +92,6 @@ int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count, const dwtfra
       delete b;
       return DWTFRAG_EINVAL;
     }
-    // batches fill the device with many items: 128-row tiles unless tuned;
     // every tile has kBatchCols columns per lane (one kernel serves all depths)
     const dwtfrag_launch *tl = tuned_launch(tune, n_tune, src.width, src.levels);
     if (tl && tl->lane_cols != 0 && tl->lane_cols != 8 && tl->lane_cols != 16) {
