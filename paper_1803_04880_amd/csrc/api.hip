@@ -143,9 +143,9 @@ int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells) {
 // for each of the 1024 SIMDs (four where the row's end cuts a lane's columns:
 // those wavefronts take 2.5 times as long a row), up to 32 rows (at four
 // levels 48).  Measured, us: 16 MiB of width 4096 at three levels 24 rows
-// 18.6, 16: 19.9, 32: 21.1; 12 MB of width 3001 at two levels 8 rows 24.6,
-// 16: 26.8, 32: 32.2; 256 MiB at three levels 32 rows 158, 24: 163, 48: 158,
-// 64: 160; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
+// 17.7, 16: 19.0, 32: 20.0; 12 MB of width 3001 at two levels 8 rows 23.9,
+// 16: 26.4, 32: 32.3; 256 MiB at three levels 32 rows 161, 24: 162, 48: 163,
+// 16: 176; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
 int inv_seg_rows(int L, int C1, int n_win, int W, int H) {
   const int unit = 1 << L, most = std::min(L == 4 ? 48 : 32, inv_max_rows(L, C1));
   const int64_t waves = W % C1 ? 4096 : 2048;

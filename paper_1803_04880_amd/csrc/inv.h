@@ -20,9 +20,9 @@
 // What bounds it is HBM at large sizes; at an image's size each SIMD has one
 // or two wavefronts, and it is their latency.  Measured against a wavefront
 // per long segment with LDS queues between the levels and a launch of its own
-// for the exact redo: 256 MiB at three levels 201 -> 158 us (5.1 TB/s), 16
-// MiB 35.2 -> 18.1 us, 12 MB of width 3001 at two levels 36 -> 24 us, 64 MiB
-// at six levels, both ways, 173 -> 138 us.
+// for the exact redo: 256 MiB at three levels 200 -> 162 us (5.0 TB/s), 16
+// MiB 35.2 -> 17.4 us, 12 MB of width 3001 at two levels 36 -> 24 us, 64 MiB
+// at six levels, both ways, 173 -> 133 us.
 #pragma once
 
 #include "lift.h"
@@ -292,6 +292,8 @@ struct InvWavePk {
   char *prow;              // the next output row
   int ks_off;              // this lane's bytes in a keystream row
   int ulast;               // the segment's last unit
+  const char *pHL[L + 1], *pLH[L + 1], *pHH[L + 1], *pLL;  // the rows loaded next
+  int last_h[L + 1], last_d[L + 1];                        // the last rows of HL, and of LH and HH
 
   __device__ __forceinline__ InvWavePk(SP &P_, const InvRect &B_, const int16_t *llin_, const int16_t *pub_,
                                        void *out_, const InvKeys<L, C1> &ks_, int lane_)
@@ -386,6 +388,42 @@ struct InvWavePk {
   template <int l> __device__ __forceinline__ Words<l> load_hl(int k) const {
     const int64_t at = at_hl<l>(k);
     return load_row<l>(pub + at, P.wdim[l - 1] - P.wdim[l], GEN ? pub_end() - at : 0);
+  }
+  // The ring's loads, row k of HL, of LH and HH, of LL: from pointers that
+  // move on while there is a next row (a row's address from its index is some
+  // ten scalar instructions, and a lone wavefront issues those one by one:
+  // 252 -> 157 a unit, 16 MiB at three levels 18.3 -> 17.4 us).
+  __device__ __forceinline__ static const char *advance(const char *p, bool more, int cols) {
+    return uniform_ptr(p + (more ? 2u * uint32_t(cols) : 0u));
+  }
+  __device__ __forceinline__ int64_t left_at(const char *p) const {
+    return GEN ? (reinterpret_cast<const char *>(pub + pub_end()) - p) >> 1 : 0;
+  }
+  template <int l> __device__ __forceinline__ void ring_start(int k) {
+    const int wl = P.wdim[l], wh = P.wdim[l - 1] - wl;
+    const int rows = P.hdim[l - 1] - P.hdim[l];
+    last_h[l] = min(NS<l> * ulast, P.hdim[l] - 1);
+    last_d[l] = min(NS<l> * ulast, rows - 1);
+    const int kd = max(min(k, last_d[l]), 0);
+    pHL[l] = uniform_ptr(reinterpret_cast<const char *>(pub + at_hl<l>(k)));
+    pLH[l] = uniform_ptr(reinterpret_cast<const char *>(pub + P.off_lh[l] + int64_t(kd) * wl));
+    pHH[l] = uniform_ptr(reinterpret_cast<const char *>(pub + P.off_hh[l] + int64_t(kd) * wh));
+  }
+  template <int l> __device__ __forceinline__ void next_rows(int k, Words<l> &h, Words<l> &lo, Words<l> &hi) {
+    const int wl = P.wdim[l], wh = P.wdim[l - 1] - wl;
+    h = load_row<l>(reinterpret_cast<const int16_t *>(pHL[l]), wh, left_at(pHL[l]));
+    lo = load_row<l>(reinterpret_cast<const int16_t *>(pLH[l]), wl, left_at(pLH[l]));
+    hi = load_row<l>(reinterpret_cast<const int16_t *>(pHH[l]), wh, left_at(pHH[l]));
+    pHL[l] = advance(pHL[l], k < last_h[l], wh);
+    pLH[l] = advance(pLH[l], k < last_d[l], wl);
+    pHH[l] = advance(pHH[l], k < last_d[l], wh);
+  }
+  __device__ __forceinline__ Words<L> next_ll(int k) {
+    const int wl = P.wdim[L];
+    const Words<L> w = load_row<L>(reinterpret_cast<const int16_t *>(pLL), wl,
+                                   GEN ? (reinterpret_cast<const char *>(llin + int64_t(P.hdim[L]) * wl) - pLL) >> 1 : 0);
+    pLL = advance(pLL, k < last_h[L], wl);
+    return w;
   }
   template <int l> __device__ __forceinline__ void load_d(int k, Words<l> &lo, Words<l> &hi) const {
     const int wl = P.wdim[l], wh = P.wdim[l - 1] - wl;
@@ -570,8 +608,7 @@ struct InvWavePk {
     }
     // the slot is free: the step Q ahead
     free_regs(Dv, X, chk);
-    Fh<l>()[slot] = load_hl<l>(k + Q<l>);
-    load_d<l>(k + Q<l>, Fl<l>()[slot], Fx<l>()[slot]);
+    next_rows<l>(k + Q<l>, Fh<l>()[slot], Fl<l>()[slot], Fx<l>()[slot]);
     if constexpr (l > 1) {
       uint32_t la[NP<l - 1>];
       to_ll<l>(Ra, la);
@@ -610,7 +647,7 @@ struct InvWavePk {
 #pragma unroll
     for (int j = 0; j < NP<L>; ++j) asm volatile("" : "+v"(ll[j]));
     __builtin_amdgcn_sched_barrier(0);
-    F0[slot] = load_ll(u + Q<L>);
+    F0[slot] = next_ll(u + Q<L>);
     step<L, 0, S, CHK>(u, ll);
   }
   __device__ __forceinline__ void decrypt(uint32_t (&ll)[NP<L>], int k) const {
@@ -676,10 +713,10 @@ struct InvWavePk {
     load_d<l>(k, Il<l>()[1], Ix<l>()[1]);
   }
   template <int l> __device__ __forceinline__ void ring_loads(int u0) {
+    ring_start<l>(NS<l> * u0 + 1);
 #pragma unroll
     for (int q = 0; q < Q<l>; ++q) {
-      Fh<l>()[q] = load_hl<l>(NS<l> * u0 + 1 + q);
-      load_d<l>(NS<l> * u0 + 1 + q, Fl<l>()[q], Fx<l>()[q]);
+      next_rows<l>(NS<l> * u0 + 1 + q, Fh<l>()[q], Fl<l>()[q], Fx<l>()[q]);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -696,8 +733,10 @@ struct InvWavePk {
     if constexpr (L >= 2) init_loads<2>(u0);
     init_loads<1>(u0);
     __builtin_amdgcn_sched_barrier(0);
+    last_h[L] = min(ulast, P.hdim[L] - 1);
+    pLL = uniform_ptr(reinterpret_cast<const char *>(llin + int64_t(min(u0 + 1, last_h[L])) * P.wdim[L]));
 #pragma unroll
-    for (int q = 0; q < Q<L>; ++q) F0[q] = load_ll(u0 + 1 + q);
+    for (int q = 0; q < Q<L>; ++q) F0[q] = next_ll(u0 + 1 + q);
     if constexpr (L >= 4) ring_loads<4>(u0);
     if constexpr (L >= 3) ring_loads<3>(u0);
     if constexpr (L >= 2) ring_loads<2>(u0);
