@@ -69,8 +69,8 @@ def percentile(xs, q):
 
 
 # sources of the kernels and launch planning the plain protect / restore runs
-PLAIN_PATH_SOURCES = ("api.hip", "common.h", "fwd.h", "fwd.hip", "inv.h", "inv.hip",
-                      "lift.h", "pack.h")
+PLAIN_PATH_SOURCES = ("api.hip", "common.h", "fwd.h", "fwd.hip", "fwd_kernel.h", "inv.h", "inv.hip",
+                      "inv_kernel.h", "lift.h", "pack.h")
 BATCH_PATH_SOURCES = PLAIN_PATH_SOURCES + ("batch.h", "batch.hip", "fwd_batch.hip",
                                              "inv_batch.hip")
 

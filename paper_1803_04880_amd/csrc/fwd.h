@@ -28,7 +28,7 @@
 // wavefront per long segment with LDS queues between the levels, which
 // waited for its own stores every batch: 256 MiB at three levels 231 -> 177
 // us (4.6 TB/s), 16 MiB 46.5 -> 18.4, 12 MB of width 3001 at two levels 65 ->
-// 25; one 16 MiB wavefront per SIMD issues for about 13 of its 18 us.
+// 20; one 16 MiB wavefront per SIMD issues for about 13 of its 18 us.
 #pragma once
 
 #include "lift.h"
@@ -62,11 +62,16 @@ template <class SP> __device__ __forceinline__ int fwd_ks_blocks(SP &G, const Fw
   return ((2 * cols + 30) >> 4);
 }
 
-// GEN: windows whose right end cuts a lane's columns, and wavefronts that
-// read the partial last row of the view: per-lane edge masks, element-wise
-// stores of cut lanes and checked loads.  All others run the plain form,
-// where an edge of the row can only lie at a lane's boundary.
-template <int L, int C1, bool U8IN, bool GEN, class SP>
+// GEN: windows whose right end cuts a lane's columns, and without TAIL
+// wavefronts that read the view's partial last row: per-lane edge masks, cut
+// lanes stored in pieces, checked loads.  All others run the plain form, where
+// an edge of the row can only lie at a lane's boundary.
+// TAIL: the kernels of views with a partial last row.  Their plain form checks
+// for that row by itself: the general one takes twice as long a row, and a
+// launch lasts as long as its last segment (16 MiB of width 4088, three levels
+// 37.0 -> 21.3 us).  Kernels of whole views stay without the checks, which
+// cost 6% (16 MiB of width 4096 18.3 -> 19.5 us).
+template <int L, int C1, bool U8IN, bool GEN, bool TAIL, class SP>
 struct FwdWave {
   template <int l> static constexpr int M = (C1 >> (l - 1)) / 2;  // evens per lane at level l
   template <int l> static constexpr int NP = Pk<M<l>>::P;         // packed regs per parity
@@ -91,6 +96,7 @@ struct FwdWave {
   // a comparison: those end up in vector registers)
   int keep1;
   int rlast;              // last row streamed
+  int tail_last;          // last_col of the view's last row
   uint32_t q[PF][RW];     // rows in flight
 
   // per-level registers: previous even row, previous high row
@@ -120,34 +126,76 @@ struct FwdWave {
     const int64_t at = int64_t(r) * G.W;
     const char *rowp = static_cast<const char *>(in) + at * (U8IN ? 1 : 2);
     if constexpr (GEN) {
-      const gptr<const char> src = glob(rowp);
-      if (at + B.cbase + 64 * C1 > G.n_valid) {  // zeros outside the view
-        const int64_t nv = min(int64_t(G.W - c0), G.n_valid - at - c0);
-#pragma unroll
-        for (int i = 0; i < RW; ++i) w[i] = 0;
-#pragma unroll
-        for (int t = 0; t < C1; ++t)
-          if (t < nv) {
-            if constexpr (U8IN) w[t >> 2] |= uint32_t(((gptr<const uint8_t>)src)[c0 + t]) << (8 * (t & 3));
-            else w[t >> 1] |= uint32_t(((gptr<const uint16_t>)src)[c0 + t]) << (16 * (t & 1));
-          }
+      if (G.n_valid < C1) {  // less than a lane reads: one by one
+        load_tiny(rowp, at, w);
         return;
       }
+      // lanes past the view's end read its last samples, and the row's use
+      // shifts them into place (realign)
+      const int last = last_col(at), base = min(last, 0);
+      load_at(rowp + base * ES, uint32_t((min(c0, last) - base) * ES), w);
+    } else if constexpr (!TAIL) {
+      load_at(rowp, voff, w);
+    } else {  // the same for the last row
+      const bool tail = r == G.H - 1;
+      load_at(rowp + (tail ? min(tail_last, 0) * ES : 0),
+              min(voff, tail ? uint32_t(max(tail_last, 0) * ES) : 0x7FFFFFFFu), w);
     }
-    load_vec(rowp, w);
   }
-  // This lane's columns of the row at rowp.
-  __device__ __forceinline__ void load_vec(const char *rowp, uint32_t (&w)[RW]) const {
+  static constexpr int ES = U8IN ? 1 : 2;
+  // Last column (negative: before the row) of the row at `at` from which C1
+  // samples may be read.
+  __device__ __forceinline__ int last_col(int64_t at) const {
+    return int(min(G.n_valid - at - C1, int64_t(1) << 28));
+  }
+  __device__ __forceinline__ void load_tiny(const char *rowp, int64_t at, uint32_t (&w)[RW]) const {
+#pragma unroll
+    for (int i = 0; i < RW; ++i) w[i] = 0;
+#pragma unroll 1
+    for (int t = C1 - 1; t >= 0; --t) {
+#pragma unroll
+      for (int i = RW - 1; i > 0; --i) w[i] = __builtin_amdgcn_alignbit(w[i], w[i - 1], 32 - 8 * ES);
+      w[0] <<= 8 * ES;
+      if (c0 + t < G.W && at + c0 + t < G.n_valid) {
+        if constexpr (U8IN) w[0] |= ((gptr<const uint8_t>)glob(rowp))[c0 + t];
+        else w[0] |= ((gptr<const uint16_t>)glob(rowp))[c0 + t];
+      }
+    }
+  }
+  // Row r as loaded -> its samples in place, zeros past the view's end.
+  __device__ __forceinline__ void realign(int r, uint32_t (&w)[RW]) const {
+    r = min(r < 0 ? -r : r, rlast);
+    int last;
+    if constexpr (GEN) {
+      last = last_col(int64_t(r) * G.W);
+      if (last >= G.W || G.n_valid < C1) return;
+    } else {
+      if (r != G.H - 1) return;
+      last = tail_last;
+    }
+    const int sh = min(max(c0 - last, 0), C1) * ES;  // bytes
+#pragma unroll
+    for (int b = 1; b <= 4 * RW; b *= 2)
+#pragma unroll
+      for (int i = 0; i < RW; ++i) {
+        const int up = b / 4;
+        const uint32_t v = b < 4 ? __builtin_amdgcn_alignbit(i + 1 < RW ? w[i + 1 < RW ? i + 1 : i] : 0u, w[i], 8 * (b & 3))
+                                 : (i + up < RW ? w[i + up < RW ? i + up : i] : 0u);
+        w[i] = (sh & b) ? v : w[i];
+      }
+  }
+  // C1 samples at byte off of the row at rowp.
+  __device__ __forceinline__ void load_at(const char *rowp, uint32_t off, uint32_t (&w)[RW]) const {
     // (the address stays in scalar registers: the lane's offset is all of its
     // vector part)
     const gptr<const char> src = glob(uniform_ptr(rowp));
     if constexpr (RW == 2) {
-      const u32x2 v = *(gptr<const u32x2_u>)(src + voff);
+      const u32x2 v = *(gptr<const u32x2_u>)(src + off);
       w[0] = v.x; w[1] = v.y;
     } else {
 #pragma unroll
       for (int i = 0; i < RW; i += 4) {
-        const u32x4 v = *(gptr<const u32x4_u>)(src + voff + 4u * i);
+        const u32x4 v = *(gptr<const u32x4_u>)(src + off + 4u * i);
         w[i] = v.x; w[i + 1] = v.y; w[i + 2] = v.z; w[i + 3] = v.w;
       }
     }
@@ -241,12 +289,13 @@ struct FwdWave {
     uint32_t Ein[NP<l>], Oin[NP<l>];
     if constexpr (l == 1) {
       constexpr int slot = (kWarm<0> + S * U + J) % PF;
+      if constexpr (CHK && (GEN || TAIL)) realign(U * v - 1 + J, q[slot]);
       unpack(q[slot], Ein, Oin);
       free_slot(Ein, Oin);
       if constexpr (CHK) {
         load_row(U * v - 1 + J + PF, q[slot]);
       } else {
-        load_vec(pnext, q[slot]);
+        load_at(pnext, voff, q[slot]);
         pnext += int64_t(G.W) * (U8IN ? 1 : 2);
       }
     } else {
@@ -286,6 +335,7 @@ struct FwdWave {
     uint32_t Ein[NP<l>], Oin[NP<l>];
     if constexpr (l == 1) {
       constexpr int slot = i % PF;
+      if constexpr (GEN) realign(r0 + i, q[slot]);
       unpack(q[slot], Ein, Oin);
       free_slot(Ein, Oin);
       load_row(r0 + i + PF, q[slot]);
@@ -428,6 +478,7 @@ struct FwdWave {
     voff = uint32_t(GEN ? c0 : min(c0, G.W - C1)) * (U8IN ? 1u : 2u);
     redge = c0 + C1 == G.W;
     rlast = min(G.H, B.Y1 + U) - 1;
+    tail_last = last_col(int64_t(G.H - 1) * G.W);
     const int v0 = B.Y0 >> L;
     const int r0 = U * v0 - 1 - kWarm<0>;  // first warm-up row
     if (v0 > 0) {
@@ -469,8 +520,9 @@ struct FwdWave {
     int v = v0 + 1;
     {
       // whole trips of units that touch no edge, nor does what they prefetch
-      // (general form: nor rows that a window reaches past the view from)
-      const int rvec = GEN ? min(rlast, G.H - 3 - 64 * C1 / G.W) : rlast;
+      // (tail: nor the partial last row; general form: nor rows that a window
+      // reaches past the view from)
+      const int rvec = GEN ? min(rlast, G.H - 3 - 64 * C1 / G.W) : TAIL ? min(rlast, G.H - 2) : rlast;
       const int end = min(v1, (rvec + 2 - PF) >> L);
       if (v == 1 && v + UPL <= end) {  // (the second unit still holds top rows)
         trip<true>(v, v1);
@@ -533,13 +585,13 @@ __device__ __forceinline__ void fwd_keystream(SP &G, const FwdRect &B, uint32_t 
   }
 }
 
-// Whether a wavefront needs the general form: its window's end cuts a lane,
-// or its last row is the view's partial one and the window reaches into the
-// missing part.
-template <int L, int C1, class SP>
+// Whether a wavefront needs the general form (also where the view holds less
+// than a lane reads).
+template <int L, int C1, bool TAIL, class SP>
 __device__ __forceinline__ bool fwd_is_general(SP &G, const FwdRect &B) {
   const int end = B.cbase + 64 * C1;
-  if (end > G.W && G.W % C1 != 0) return true;
+  if ((end > G.W && G.W % C1 != 0) || G.n_valid < C1) return true;
+  if constexpr (TAIL) return false;
   const int64_t last = int64_t(min(G.H, B.Y1 + (1 << L)) - 1) * G.W;
   return last + min(G.W, end) > G.n_valid;
 }
@@ -547,14 +599,14 @@ __device__ __forceinline__ bool fwd_is_general(SP &G, const FwdRect &B) {
 // One wavefront's rectangle.  `tables` makes the AES tables and keys of the
 // workgroup ready (every wavefront of it passes there, also one without a
 // rectangle); the first rows are in flight meanwhile.
-template <int L, int C1, bool U8IN, class SP, class Tables>
+template <int L, int C1, bool U8IN, bool TAIL, class SP, class Tables>
 __device__ __forceinline__ void fwd_rect(SP &G, int wave, const void *in, int16_t *pub,
                                          int16_t *llout, uint32_t *ks, const uint32_t *te,
                                          const uint32_t *kw, int lane, const Tables &tables) {
   const bool live = wave < G.n_waves;
   const FwdRect B(G, live ? wave : 0);
-  const bool general = fwd_is_general<L, C1>(G, B);
-  FwdWave<L, C1, U8IN, false, SP> w{G, B, in, ks, llout, lane};
+  const bool general = fwd_is_general<L, C1, TAIL>(G, B);
+  FwdWave<L, C1, U8IN, false, TAIL, SP> w{G, B, in, ks, llout, lane};
   w.pub8 = reinterpret_cast<char *>(pub);
   if (live && !general) w.start();
   if (G.use_aes) tables();
@@ -564,7 +616,7 @@ __device__ __forceinline__ void fwd_rect(SP &G, int wave, const void *in, int16_
     wave_lds_sync();
   }
   if (general) {
-    FwdWave<L, C1, U8IN, true, SP> g{G, B, in, ks, llout, lane};
+    FwdWave<L, C1, U8IN, true, TAIL, SP> g{G, B, in, ks, llout, lane};
     g.pub8 = reinterpret_cast<char *>(pub);
     g.start();
     g.run();

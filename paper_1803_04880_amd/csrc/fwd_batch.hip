@@ -14,7 +14,7 @@ constexpr int kFwdBatchKs = cmax(cmax(fwd_ks_words(1, kBatchCols), fwd_ks_words(
 template <int L>
 __device__ __forceinline__ void fwd_batch_tile(ConstItem &it, int wave, uint32_t *ks,
                                                const uint32_t *te, const uint32_t *kw, int lane) {
-  fwd_rect<L, kBatchCols, true>(it.fwd, wave, it.in, it.pub, reinterpret_cast<int16_t *>(it.priv), ks,
+  fwd_rect<L, kBatchCols, true, false>(it.fwd, wave, it.in, it.pub, reinterpret_cast<int16_t *>(it.priv), ks,
                                 te, kw, lane, [] {});
 }
 

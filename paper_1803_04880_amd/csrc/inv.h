@@ -256,12 +256,15 @@ template <> struct RowWords<1> {
 // the rectangle with the 32-bit stream (same output bytes as the exact
 // integer inverse for any fragments).
 //
-// GEN: windows whose right end cuts a lane's columns, wavefronts that write
-// the partial last row of the view, and levels of one row: per-lane edge
-// masks, cut lanes stored in pieces, checked loads at the ends of the
-// fragments.  All others run the plain form, where an edge of the row can
-// only lie at a lane's boundary.
-template <int L, int C1, bool U8OUT, bool GEN, class SP>
+// GEN: windows whose right end cuts a lane's columns, levels of one row, and
+// without TAIL wavefronts that write the view's partial last row: per-lane
+// edge masks, cut lanes stored in pieces, checked loads at the ends of the
+// fragments.  All others run the plain form, where an edge of the row can only
+// lie at a lane's boundary.
+// TAIL: the kernels of views with a partial last row, whose plain form stores
+// that row in pieces by itself (16 MiB of width 4088 at three levels 35.5 ->
+// 18.7 us; in the kernels of whole views the checks would cost 3%).
+template <int L, int C1, bool U8OUT, bool GEN, bool TAIL, class SP>
 struct InvWavePk {
   template <int l> static constexpr int M = (C1 >> (l - 1)) / 2;  // evens per lane at level l
   template <int l> static constexpr int NP = Pk<M<l>>::P;         // words per parity
@@ -505,7 +508,8 @@ struct InvWavePk {
     }
   }
   // Output row: keep is -1 where the row is owned, i its index.
-  __device__ __forceinline__ void put_row(const uint32_t (&x)[R<1>], int i, int keep) {
+  // LAST: it may be the view's last row.
+  template <bool LAST> __device__ __forceinline__ void put_row(const uint32_t (&x)[R<1>], int i, int keep) {
     uint32_t E[NP<1>], O[NP<1>];
     lift_row<1>(x, E, O);
     constexpr int ES = U8OUT ? 1 : 2, RB = C1 * ES, RWd = RB / 4;
@@ -520,13 +524,13 @@ struct InvWavePk {
         w[2 * q + 1] = hi_halves(E[q], O[q]);
       }
     }
-    int cols = P.W;
-    if constexpr (GEN) cols = int(min(int64_t(P.W), max(int64_t(0), P.n_valid - int64_t(i) * P.W)));
+    const bool part = LAST && (GEN || TAIL) && i == P.H - 1;
+    const int cols = part ? int(P.n_valid - int64_t(P.H - 1) * P.W) : P.W;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
         uniform_ptr(prow), 0, __builtin_amdgcn_readfirstlane((cols * ES) & keep), 0x00027000);
     prow = uniform_ptr(prow + int64_t(P.W) * ES);
     uint32_t off = so;
-    if constexpr (GEN) {
+    if (GEN || part) {
       // a lane that the row's end cuts stores its first nv bytes in pieces of
       // 16, 8, 4, 2 and 1, where nv has that bit
       const int nv = (cols - c0) * ES;
@@ -617,8 +621,8 @@ struct InvWavePk {
       step<l - 1, 2 * J + 1, S, CHK>(u, la);
     } else {
       const int end = B.last_seg ? P.H : B.Y1;
-      put_row(Ra, 2 * k - 1, CHK ? (2 * k - 1 - end) >> 31 : -1);
-      put_row(X, 2 * k, CHK ? (2 * k - end) >> 31 : -1);
+      put_row<CHK>(Ra, 2 * k - 1, CHK ? (2 * k - 1 - end) >> 31 : -1);
+      put_row<CHK>(X, 2 * k, CHK ? (2 * k - end) >> 31 : -1);
     }
   }
   // A copy in a register of its own: without it the previous high row keeps
@@ -703,7 +707,7 @@ struct InvWavePk {
       to_ll<l>(Xv, la);
       init<l - 1>(u0, la);
     } else {
-      put_row(Xv, 2 * k, -1);
+      put_row<true>(Xv, 2 * k, -1);
     }
   }
   template <int l> __device__ __forceinline__ void init_loads(int u0) {
@@ -788,28 +792,25 @@ struct InvWavePk {
   }
 };
 
-// Whether a wavefront needs the general form: its window's end cuts a lane, a
-// level has one row (no LH / HH rows), or the rectangle holds the view's
-// partial last row.
-template <int L, int C1, class SP>
+// Whether a wavefront needs the general form.
+template <int L, int C1, bool TAIL, class SP>
 __device__ __forceinline__ bool inv_is_general(SP &G, const InvRect &B) {
-  if (B.cbase + 64 * C1 > G.W && G.W % C1 != 0) return true;
-  if (G.hdim[L - 1] < 2) return true;
-  return B.last_seg && G.n_valid < int64_t(G.H) * G.W;
+  if ((B.cbase + 64 * C1 > G.W && G.W % C1 != 0) || G.hdim[L - 1] < 2) return true;
+  return !TAIL && B.last_seg && G.n_valid < int64_t(G.H) * G.W;
 }
 
 // One wavefront's rectangle.  `tables` makes the AES tables and keys of the
 // workgroup ready (every wavefront of it passes there, also one without a
 // rectangle); the first rows are in flight meanwhile.
-template <int L, int C1, bool U8OUT, class SP, class Tables>
+template <int L, int C1, bool U8OUT, bool TAIL, class SP, class Tables>
 __device__ __forceinline__ void inv_rect(SP &G, int wave, const int16_t *llin, const int16_t *pub,
                                          void *out, uint32_t *lds, const uint32_t *te,
                                          const uint32_t *kw, int lane, const Tables &tables) {
   const bool live = wave < G.n_waves;
   const InvRect B(G, live ? wave : 0);
-  const bool general = inv_is_general<L, C1>(G, B);
+  const bool general = inv_is_general<L, C1, TAIL>(G, B);
   const InvKeys<L, C1> ks(G, B, lds, B.Y0 >> L);
-  InvWavePk<L, C1, U8OUT, false, SP> w{G, B, llin, pub, out, ks, lane};
+  InvWavePk<L, C1, U8OUT, false, TAIL, SP> w{G, B, llin, pub, out, ks, lane};
   if (live && !general) w.start();
   if (G.use_aes) tables();
   if (!live) return;
@@ -823,7 +824,7 @@ __device__ __forceinline__ void inv_rect(SP &G, int wave, const int16_t *llin, c
     // (fragments of fewer values than a lane reads: the exact stream)
     if (G.off_hh[1] + int64_t(G.hdim[0] - G.hdim[1]) * (G.wdim[0] - G.wdim[1]) >= C1 / 2 &&
         int64_t(G.hdim[L]) * G.wdim[L] >= max(1, C1 >> L)) {
-      InvWavePk<L, C1, U8OUT, true, SP> g{G, B, llin, pub, out, ks, lane};
+      InvWavePk<L, C1, U8OUT, true, TAIL, SP> g{G, B, llin, pub, out, ks, lane};
       g.start();
       ok = g.run();
     }

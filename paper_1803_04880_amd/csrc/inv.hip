@@ -1,42 +1,20 @@
 // Inverse launches of single buffers (the streaming code is in inv.h).
-#include "inv.h"
+#include "inv_kernel.h"
 
 namespace dwtfrag {
 
-template <int L, int C1, bool U8OUT>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(C1 == 16 ? 3 : 4)))
-void inv_kernel(const int16_t *__restrict__ llin, const int16_t *__restrict__ pub,
-                void *__restrict__ out, const StageParams P) {
-  __shared__ uint32_t s_ks[kWavesPerBlock][inv_ks_words(L, C1)];
-  __shared__ uint32_t s_te[1024];
-  __shared__ uint32_t s_kw[kKeyWords];
-  // the wavefront index is uniform; readfirstlane lets the compiler see that,
-  // so all row / level bookkeeping derived from it stays scalar
-  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave = blockIdx.x * (blockDim.x >> 6) + wib;
-  AesLoad aes;
-  if (P.use_aes) aes.issue(P.key);
-  inv_rect<L, C1, U8OUT>(P, wave, llin, pub, out, s_ks[wib], s_te, s_kw, int(threadIdx.x & 63), [&]() {
-    aes.finish(s_te, s_kw);
-    __syncthreads();
-  });
-}
-
-template <int L, int C1, bool U8OUT>
-static hipError_t launch_inv_t(const int16_t *llin, const int16_t *pub, void *out,
-                               const StageParams &P, hipStream_t s) {
-  const int per = block_waves(P.n_waves);
-  hipLaunchKernelGGL((inv_kernel<L, C1, U8OUT>), dim3((P.n_waves + per - 1) / per), dim3(64 * per), 0,
-                     s, llin, pub, out, P);
-  return hipGetLastError();
-}
+hipError_t launch_inv_tail(int L, int C1, const int16_t *llin, const int16_t *pub, void *out,
+                           const StageParams &P, hipStream_t s);
 
 hipError_t launch_inv(int L, int C1, bool u8out, const int16_t *llin, const int16_t *pub,
                       void *out, const StageParams &P, hipStream_t s) {
+  // (four levels, where the checks for a partial row spill registers, and
+  // int16 stages, which are whole, have no such kernels)
+  if (L < 4 && P.n_valid < int64_t(P.H) * P.W) return launch_inv_tail(L, C1, llin, pub, out, P, s);
 #define DWTFRAG_CASE(LL, CC)                                                   \
   if (L == LL && C1 == CC)                                                     \
-    return u8out ? launch_inv_t<LL, CC, true>(llin, pub, out, P, s)            \
-                 : launch_inv_t<LL, CC, false>(llin, pub, out, P, s);
+    return u8out ? launch_inv_t<LL, CC, true, false>(llin, pub, out, P, s)            \
+                 : launch_inv_t<LL, CC, false, false>(llin, pub, out, P, s);
   DWTFRAG_CASE(1, 8) DWTFRAG_CASE(2, 8) DWTFRAG_CASE(3, 8)
   DWTFRAG_CASE(1, 16) DWTFRAG_CASE(2, 16) DWTFRAG_CASE(3, 16) DWTFRAG_CASE(4, 16)
 #undef DWTFRAG_CASE

@@ -14,7 +14,7 @@ constexpr int kInvBatchKs = cmax(cmax(inv_ks_words(1, kBatchCols), inv_ks_words(
 template <int L>
 __device__ __forceinline__ void inv_batch_tile(ConstItem &it, int wave, uint32_t *ks,
                                                const uint32_t *te, const uint32_t *kw, int lane) {
-  inv_rect<L, kBatchCols, true>(it.inv, wave, reinterpret_cast<const int16_t *>(it.priv), it.pub,
+  inv_rect<L, kBatchCols, true, false>(it.inv, wave, reinterpret_cast<const int16_t *>(it.priv), it.pub,
                                 it.out, ks, te, kw, lane, [] {});
 }
 

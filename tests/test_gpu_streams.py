@@ -128,3 +128,14 @@ def test_values_outside_the_packed_range_at_row_ends(width, levels):
         tq = torch.from_numpy(pub).to(DEV)
         got = dwtfrag.restore(tp, tq, n, width, levels, key, nonce).cpu().numpy().tobytes()
         assert got == fragment.restore(priv, pub.tobytes(), n, width, levels, key, nonce)
+
+
+@pytest.mark.parametrize("levels,cols", [(1, 8), (2, 8), (3, 8), (1, 16), (2, 16), (3, 16)])
+@pytest.mark.parametrize("height", [1, 2, 9, 41])
+def test_partial_last_row_of_whole_lanes(levels, cols, height):
+    """Rows of whole lanes (no window cuts one), the last row ending in the
+    first lane, at and around a lane's boundary, in the last lane; in one
+    window and in several."""
+    for width in (8 * cols, 64 * cols, 150 * cols):
+        for rest in (1, cols - 1, cols, cols + 1, width - cols, width - 1):
+            _check((height - 1) * width + rest, width, levels, (0, cols))
