@@ -841,9 +841,11 @@ __global__ __launch_bounds__(64 * NW) void linv_level_kernel(LvCoef src, Dst dst
 // x 4096 at 4 / 8 / 16 wavefronts, us: 4096 tiles forward 75.5 / 76.8 / -,
 // inverse 96.6 / 88.6 / -; 1024 tiles 26.6 / 24.5 / 25.4 and 32.3 / 27.9 /
 // 28.2; 256 tiles 15.6 / 10.9 / 9.3 and 19.6 / 12.5 / 10.3.
+// Sixteen streams of such images, protect / restore of 64: 4 / 4 / 4 wavefronts
+// 4.64 / 5.58 ms, these 4.78 / 5.37, the inverse's 256 tiles at 16 5.67.
 template <int N> struct Waves { static constexpr int value = N; };
 inline int fwd_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : tiles <= 2048 ? 8 : 4; }
-inline int inv_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : 8; }
+constexpr int kInvLevelWaves = 8;
 
 template <class Src>
 hipError_t fwd_level(Src src, const LvBands &out, const Net &net, int h, int w, hipStream_t s) {
@@ -865,12 +867,8 @@ hipError_t inv_level(const LvCoef &src, Dst dst, const Net &net, int h, int w, h
   const int tx = (w + kLvW - 1) / kLvW, ty = (h + kInvH - 1) / kInvH;
   const int64_t grid = int64_t(tx) * ty;
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  const auto go = [&](auto nw) {
-    constexpr int NW = decltype(nw)::value;
-    hipLaunchKernelGGL((linv_level_kernel<Dst, NW>), dim3(unsigned(grid)), dim3(64 * NW), 0, s, src, dst,
-                       net, h, w, tx);
-  };
-  inv_level_waves(grid) == 16 ? go(Waves<16>{}) : go(Waves<8>{});
+  hipLaunchKernelGGL((linv_level_kernel<Dst, kInvLevelWaves>), dim3(unsigned(grid)),
+                     dim3(64 * kInvLevelWaves), 0, s, src, dst, net, h, w, tx);
   return hipGetLastError();
 }
 
