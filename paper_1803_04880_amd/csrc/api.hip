@@ -50,12 +50,6 @@ void expand_key(const uint8_t key[16], const uint8_t nonce[16], AesKey *out) {
 
 namespace {
 
-// Rows and columns of a view.  The launch planning and the kernels index rows
-// and columns in int32 with margins of up to a window (1024 columns) and a
-// unit plus halos (under 64 rows) past the end, so the limit keeps 2^16 below
-// 2^31.
-constexpr uint64_t kMaxDim = 0x7FFF0000ull;
-
 // Bytes of the static workspace behind dwtfrag_protect_noalloc (16 MiB).
 constexpr uint64_t kScratchBytes = uint64_t(16) << 20;
 
@@ -78,9 +72,9 @@ uint64_t align256(uint64_t v) { return (v + 255) & ~uint64_t(255); }
 
 int make_geometry(uint64_t n, uint32_t width, uint32_t levels, Geometry *g) {
   if (n == 0 || width == 0 || levels == 0 || levels > kMaxLevels) return DWTFRAG_EINVAL;
-  if (width > kMaxDim) return DWTFRAG_ERANGE;
+  if (width > uint32_t(kMaxDim)) return DWTFRAG_ERANGE;
   const uint64_t H = (n + width - 1) / width;
-  if (H > kMaxDim) return DWTFRAG_ERANGE;
+  if (H > uint64_t(kMaxDim)) return DWTFRAG_ERANGE;
   if (H * uint64_t(width) > (uint64_t(1) << 62)) return DWTFRAG_ERANGE;
   g->n = n;
   g->W = width;

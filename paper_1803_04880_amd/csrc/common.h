@@ -233,6 +233,26 @@ constexpr int block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBl
 // space so that it comes by scalar loads.
 using ConstStage = const __attribute__((address_space(4))) StageParams;
 
+// Rows and columns of a view.  The launch planning and the kernels index rows
+// and columns in int32 with margins of up to a window (1024 columns) and a
+// unit plus halos (under 64 rows) past the end, so the limit keeps 2^16 below
+// 2^31.
+constexpr int32_t kMaxDim = 0x7FFF0000;
+
+// Reads of a lane's `span` samples at the end of a view of n_valid elements.
+// last_read_col: the last column (negative: before the row) of the row at
+// element `at` from which they may be read, kMaxDim where that lies further on
+// than any row is wide.  A lane past that column reads from there, and
+// read_shift is by how many samples it then moves them down.
+__host__ __device__ constexpr int last_read_col(int64_t n_valid, int64_t at, int span) {
+  const int64_t left = n_valid - at;
+  return int(left < kMaxDim + span ? left : kMaxDim + span) - span;
+}
+__host__ __device__ constexpr int read_shift(int c0, int last, int span) {
+  const int past = c0 - last > 0 ? c0 - last : 0;
+  return past < span ? past : span;
+}
+
 // First level-0 row of segment s (s == n_seg gives units * unit_rows).
 template <class SP> __device__ __forceinline__ int seg_start(SP &P, int s) {
   return P.unit_rows * int((int64_t(s) * P.units) / P.n_seg);

@@ -143,11 +143,7 @@ struct FwdWave {
     }
   }
   static constexpr int ES = U8IN ? 1 : 2;
-  // Last column (negative: before the row) of the row at `at` from which C1
-  // samples may be read.
-  __device__ __forceinline__ int last_col(int64_t at) const {
-    return int(min(G.n_valid - at - C1, int64_t(1) << 28));
-  }
+  __device__ __forceinline__ int last_col(int64_t at) const { return last_read_col(G.n_valid, at, C1); }
   __device__ __forceinline__ void load_tiny(const char *rowp, int64_t at, uint32_t (&w)[RW]) const {
 #pragma unroll
     for (int i = 0; i < RW; ++i) w[i] = 0;
@@ -173,7 +169,7 @@ struct FwdWave {
       if (r != G.H - 1) return;
       last = tail_last;
     }
-    const int sh = min(max(c0 - last, 0), C1) * ES;  // bytes
+    const int sh = read_shift(c0, last, C1) * ES;  // bytes
 #pragma unroll
     for (int b = 1; b <= 4 * RW; b *= 2)
 #pragma unroll
