@@ -173,6 +173,8 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   int C1 = (launch && launch->lane_cols) ? int(launch->lane_cols) : (wide ? 16 : 8);
   if (C1 != 8 && C1 != 16) return DWTFRAG_EINVAL;
   if (L == 4) C1 = 16;
+  // (a launch of more than 2^30 rows: 16 columns' segments would be too many)
+  if (alone && L == 1 && g.h[lv0] / fwd_max_rows(L, C1) >= uint64_t(kMaxLaunchWaves)) C1 = 8;
   P->H = int32_t(g.h[lv0]);
   P->W = int32_t(g.w[lv0]);
   P->n_valid = (s == 0) ? int64_t(g.n) : int64_t(g.h[lv0] * g.w[lv0]);
@@ -215,7 +217,9 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
                        : inv_seg_rows(L, C1, P->n_win, P->W, P->H);
   if (launch && launch->seg_rows)
     rows = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
-  rows = std::min(rows, forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1));
+  const int most = forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1);
+  rows = std::min(rows, most);
+  if (alone && int64_t(P->n_win) * ((P->H + rows - 1) / rows) > kMaxLaunchWaves) rows = most;
   const int64_t n_seg = (int64_t(P->H) + rows - 1) / rows;
   P->n_seg = int32_t(std::min<int64_t>(std::max<int64_t>(n_seg, 1), P->units));
   const int64_t waves = int64_t(P->n_win) * P->n_seg;

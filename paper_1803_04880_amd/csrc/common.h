@@ -207,6 +207,12 @@ struct StageParams {
   AesKey key;
 };
 
+// Rows and columns of a view.  The launch planning and the kernels index rows
+// and columns in int32 with margins of up to a window (1024 columns) and a
+// unit plus halos (under 64 rows) past the end, so the limit keeps 2^16 below
+// 2^31.
+constexpr int32_t kMaxDim = 0x7FFF0000;
+
 // Forward kernel: the rows of a segment are limited by the keystream that a
 // wavefront holds in LDS: 16 LL rows (8 at four levels, and at one level of
 // 16 columns a lane), under 9 KiB, so that four workgroups fit a compute
@@ -228,16 +234,16 @@ constexpr int inv_ks_words(int L, int C1) {
 // the AES lookups), else four.
 constexpr int block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBlock; }
 
+// Most wavefronts of a launch: HIP takes fewer than 2^32 work-items per grid
+// dimension (with the last workgroup's idle wavefronts counted).  Segments of
+// the tallest kind at 8 columns a lane keep every height below it.
+constexpr int32_t kMaxLaunchWaves = (1 << 26) - kWavesPerBlock;
+static_assert(kMaxDim / fwd_max_rows(1, 8) < kMaxLaunchWaves, "the tallest view in one launch");
+
 // A stage's parameters as the kernels take them (SP below): a kernel argument,
 // or an entry of a batch's item table, read through the constant address
 // space so that it comes by scalar loads.
 using ConstStage = const __attribute__((address_space(4))) StageParams;
-
-// Rows and columns of a view.  The launch planning and the kernels index rows
-// and columns in int32 with margins of up to a window (1024 columns) and a
-// unit plus halos (under 64 rows) past the end, so the limit keeps 2^16 below
-// 2^31.
-constexpr int32_t kMaxDim = 0x7FFF0000;
 
 // Reads of a lane's `span` samples at the end of a view of n_valid elements.
 // last_read_col: the last column (negative: before the row) of the row at

@@ -77,3 +77,8 @@ def test_one_row_of_more_than_2_to_28_columns(levels):
 def test_partial_last_row_of_more_than_2_to_28_columns(levels):
     width = (1 << 28) + 4096
     _check_end(2 * width - 5, width, levels, 1)
+
+
+@pytest.mark.parametrize("levels", [1, 3])
+def test_one_column_of_more_rows_than_a_grid_of_short_segments_takes(levels):
+    _check_end(1_700_000_000, 1, levels, 0)
