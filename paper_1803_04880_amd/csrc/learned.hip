@@ -845,7 +845,8 @@ __global__ __launch_bounds__(64 * NW) void linv_level_kernel(LvCoef src, Dst dst
 // 4.64 / 5.58 ms, these 4.78 / 5.37, the inverse's 256 tiles at 16 5.67.
 template <int N> struct Waves { static constexpr int value = N; };
 inline int fwd_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : tiles <= 2048 ? 8 : 4; }
-constexpr int kInvLevelWaves = 8;
+// (8 where the launch has fewer than the 2^32 work-items that HIP takes)
+inline int inv_level_waves(int64_t tiles) { return tiles < (int64_t(1) << 23) ? 8 : 4; }
 
 template <class Src>
 hipError_t fwd_level(Src src, const LvBands &out, const Net &net, int h, int w, hipStream_t s) {
@@ -867,8 +868,12 @@ hipError_t inv_level(const LvCoef &src, Dst dst, const Net &net, int h, int w, h
   const int tx = (w + kLvW - 1) / kLvW, ty = (h + kInvH - 1) / kInvH;
   const int64_t grid = int64_t(tx) * ty;
   if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((linv_level_kernel<Dst, kInvLevelWaves>), dim3(unsigned(grid)),
-                     dim3(64 * kInvLevelWaves), 0, s, src, dst, net, h, w, tx);
+  const auto go = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value;
+    hipLaunchKernelGGL((linv_level_kernel<Dst, NW>), dim3(unsigned(grid)), dim3(64 * NW), 0, s, src, dst,
+                       net, h, w, tx);
+  };
+  inv_level_waves(grid) == 8 ? go(Waves<8>{}) : go(Waves<4>{});
   return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@ import torch  # noqa: E402
 
 import paper_1803_04880_amd as dwtfrag  # noqa: E402
 from oracle import dwt53  # noqa: E402
+from paper_1803_04880_amd import learned  # noqa: E402
 
 DEV = "cuda:0"
 
@@ -82,3 +83,17 @@ def test_partial_last_row_of_more_than_2_to_28_columns(levels):
 @pytest.mark.parametrize("levels", [1, 3])
 def test_one_column_of_more_rows_than_a_grid_of_short_segments_takes(levels):
     _check_end(1_700_000_000, 1, levels, 0)
+
+
+def test_learned_column_of_more_tiles_than_a_grid_takes_at_8_wavefronts():
+    """2^23 tiles of 32 rows and more; the bytes come back."""
+    n = 300_000_001
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n)
+    x = torch.randint(0, 256, (n,), generator=gen, device=DEV, dtype=torch.uint8)
+    rng = np.random.default_rng(n)
+    net = learned.Predictor.from_arrays(rng.integers(-40, 41, (16, 8)), rng.integers(0, 400, 16),
+                                        rng.integers(-40, 41, 16), 100, 12)
+    print(f"n={n} width=1 learned", flush=True)
+    priv, pub = learned.protect(x, 1, 1, bytes(16), bytes(16), net)
+    assert torch.equal(learned.restore(priv, pub, n, 1, 1, bytes(16), bytes(16), net), x)
