@@ -201,7 +201,8 @@ int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count,
 uint64_t dwtfrag_batch_device_bytes(const dwtfrag_batch *plan);
 
 /* Copy the plan's tables into `device_plan` (device, 256-byte aligned, at
- * least dwtfrag_batch_device_bytes), asynchronously on `stream`: launches
+ * least dwtfrag_batch_device_bytes) and write its tile lists there (one small
+ * kernel), asynchronously on `stream`: launches
  * that use the plan must be ordered after it (the same stream, or a stream
  * made to wait for this one).  The host tables the copies read stay with the
  * plan; dwtfrag_batch_destroy waits for the last upload's copies before it

@@ -40,6 +40,26 @@ struct BatchCounters {
   unsigned int head, done;
 };
 
+// The tiles of one item in a direction's queue: they follow one another from
+// tile `first` of the table on.  The tables of both directions are one, in
+// queue order; a plan's host side makes only these runs, and the tile list is
+// written on the device (batch_tiles_kernel).
+struct BatchRun {
+  int64_t first;
+  int32_t item, pad;
+};
+
+// Tile t of the n runs: (item, wavefront index within the item).
+__host__ __device__ inline int2 batch_tile(const BatchRun *runs, int64_t n, int64_t t) {
+  int64_t lo = 0, hi = n;  // the last run that begins at or before t
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    if (runs[mid].first <= t) lo = mid;
+    else hi = mid;
+  }
+  return make_int2(runs[lo].item, int(t - runs[lo].first));
+}
+
 // Called by every workgroup once its wavefronts have left the tile loop: the
 // last one resets both counters for the next launch (no other workgroup pops
 // a tile any more at that point).

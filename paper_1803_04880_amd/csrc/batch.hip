@@ -3,18 +3,21 @@
 // The thesis cuts data into many fixed-size chunks (Ch. 5 section 5.2.1) and
 // its GPU runs take many chunks per call.  Here a batch is planned once on the
 // host (every item's geometry and launch plan with 16 columns per lane, and
-// one tile list per direction, longest tiles first), copied into a
-// caller-owned device buffer, and then run by one persistent launch per
-// direction that drains the direction's queue: protect = the forward drain
-// (encryption fused), restore = the inverse drain (decryption fused).  The
-// kernels reset their own queue counters when they finish, so a direction is
-// one kernel launch and can be captured in a HIP graph.
+// one queue of tiles per direction, longest first), copied into a caller-owned
+// device buffer, where a small kernel writes the tile lists, and then run by
+// one persistent launch per direction that drains the direction's queue:
+// protect = the forward drain (encryption fused), restore = the inverse drain
+// (decryption fused).  The kernels reset their own queue counters when they
+// finish, so a direction is one kernel launch and can be captured in a HIP
+// graph.
 #include "dwtfrag.h"
 
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <memory>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "batch.h"
@@ -31,6 +34,16 @@ int plan_single_stage(uint64_t n, uint32_t width, uint32_t levels, bool forward,
                       const dwtfrag_launch *launch, const AesKey &key, StageParams *P, int *L,
                       int *C1, uint64_t *priv_bytes);
 
+// The tile list of both directions from the queues' runs, a thread per tile;
+// the queue counters start at zero (the drains leave them at zero).
+__global__ __launch_bounds__(256) void batch_tiles_kernel(const BatchRun *__restrict__ runs, int64_t n_runs,
+                                                          int2 *__restrict__ tiles, int64_t n_tiles,
+                                                          BatchCounters *__restrict__ ctr) {
+  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  if (t < n_tiles) tiles[t] = batch_tile(runs, n_runs, t);
+  if (t < 2) ctr[t] = BatchCounters{0, 0};
+}
+
 }  // namespace dwtfrag
 
 using namespace dwtfrag;
@@ -38,10 +51,10 @@ using namespace dwtfrag;
 struct dwtfrag_batch {
   uint32_t count = 0;
   std::vector<BatchItem> items;
-  std::vector<int2> tiles;                 // forward queue, then inverse queue
+  std::vector<BatchRun> runs;              // forward queue, then inverse queue
   int64_t n_fwd = 0, n_inv = 0;            // tiles per direction
   int fwd_blocks = 0, inv_blocks = 0;      // persistent grid per direction
-  uint64_t off_ctr = 0, off_items = 0, off_tiles = 0, bytes = 0;
+  uint64_t off_ctr = 0, off_items = 0, off_runs = 0, off_tiles = 0, bytes = 0;
   char *dev = nullptr;                     // caller's device copy, set by upload
   hipEvent_t uploaded = nullptr;           // the last upload's copies are done
 };
@@ -66,38 +79,19 @@ int persistent_blocks(int per_cu) {
   return cus * std::max(1, per_cu);
 }
 
-}  // namespace
-
-extern "C" {
-
-int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_entry *tune,
-                         uint32_t n_tune, dwtfrag_batch **out) {
-  if (!out) return DWTFRAG_EINVAL;
-  *out = nullptr;
-  if (!items || count == 0 || count > (1u << 30) || (n_tune && !tune)) return DWTFRAG_EINVAL;
-  dwtfrag_batch *b = new (std::nothrow) dwtfrag_batch();
-  if (!b) return DWTFRAG_ERANGE;
+// Every item's plans and buffers, and the tiles of each direction counted.
+int plan_items(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_entry *tune,
+               uint32_t n_tune, dwtfrag_batch *b) {
   b->count = count;
   b->items.resize(count);
-  // tiles (item, wavefront) of every item, one list per direction
-  std::vector<int2> ft, it;
   for (uint32_t i = 0; i < count; ++i) {
     const dwtfrag_item &src = items[i];
-    if (!src.in || !src.priv || src.levels == 0 || src.levels > uint32_t(kMaxFused)) {
-      delete b;
-      return DWTFRAG_EINVAL;
-    }
+    if (!src.in || !src.priv || src.levels == 0 || src.levels > uint32_t(kMaxFused)) return DWTFRAG_EINVAL;
     const auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (!al16(src.in) || !al16(src.priv) || !al16(src.pub) || !al16(src.out)) {
-      delete b;
-      return DWTFRAG_EINVAL;
-    }
+    if (!al16(src.in) || !al16(src.priv) || !al16(src.pub) || !al16(src.out)) return DWTFRAG_EINVAL;
     // every tile has kBatchCols columns per lane (one kernel serves all depths)
     const dwtfrag_launch *tl = tuned_launch(tune, n_tune, src.width, src.levels);
-    if (tl && tl->lane_cols != 0 && tl->lane_cols != 8 && tl->lane_cols != 16) {
-      delete b;
-      return DWTFRAG_EINVAL;
-    }
+    if (tl && tl->lane_cols != 0 && tl->lane_cols != 8 && tl->lane_cols != 16) return DWTFRAG_EINVAL;
     const dwtfrag_launch ln{tl ? tl->seg_rows : 0u, uint32_t(kBatchCols)};
     AesKey key;
     expand_key(src.key, src.nonce, &key);
@@ -108,53 +102,76 @@ int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count, const dwtfra
     int rc = plan_single_stage(src.n, src.width, src.levels, true, &ln, key, &bi.fwd, &Lf, &Cf, &priv_bytes);
     if (rc == DWTFRAG_OK)
       rc = plan_single_stage(src.n, src.width, src.levels, false, &ln, key, &bi.inv, &Li, &Ci, &priv_bytes);
-    if (rc != DWTFRAG_OK) {
-      delete b;
-      return rc;
-    }
+    if (rc != DWTFRAG_OK) return rc;
     const uint64_t pub_bytes = 2 * (uint64_t(bi.fwd.H) * bi.fwd.W) - priv_bytes;
-    if (pub_bytes && !src.pub) {
-      delete b;
-      return DWTFRAG_EINVAL;
-    }
+    if (pub_bytes && !src.pub) return DWTFRAG_EINVAL;
     bi.in = src.in;
     bi.priv = src.priv;
     bi.pub = src.pub;
     bi.out = src.out;
     bi.priv_bytes = priv_bytes;
     bi.levels = int32_t(src.levels);
-    for (int w = 0; w < bi.fwd.n_waves; ++w) ft.push_back(make_int2(int(i), w));
-    for (int w = 0; w < bi.inv.n_waves; ++w) it.push_back(make_int2(int(i), w));
+    b->n_fwd += bi.fwd.n_waves;
+    b->n_inv += bi.inv.n_waves;
+    if (b->n_fwd + b->n_inv > 0x7fffffffll) return DWTFRAG_ERANGE;
   }
-  // Longest tiles first, so the short tiles of small items fill the end of a
-  // drain instead of extending it.  A tile's cost is the rows it streams
-  // (segment plus halos) times the columns of its window.
+  return DWTFRAG_OK;
+}
+
+// The queues of both directions.  Longest tiles first, so the short tiles of
+// small items fill the end of a drain instead of extending it.  A tile's cost
+// is the rows it streams (segment plus halos) times the columns of its window:
+// one cost per item, so the items are sorted and each one's tiles follow one
+// another.  A serving loop plans on its one host thread: 256 MiB at one level,
+// 20 Ki tiles a direction, takes 22 us with the upload, where tiles sorted one
+// by one and copied whole take 764; and copies of more than 16 KB from
+// pageable memory, which tile lists make common, stall a loop for 7 ms now and
+// then.
+void plan_queues(dwtfrag_batch *b) {
   const auto tile_cost = [](const StageParams &P) {
     const int64_t seg = int64_t(P.unit_rows) * ((P.units + P.n_seg - 1) / P.n_seg);
     return std::min<int64_t>(P.H, seg + P.halo_t + P.halo_b) * std::min(P.W, P.own_w);
   };
-  std::vector<int64_t> fcost(count), icost(count);
-  for (uint32_t i = 0; i < count; ++i) {
-    fcost[i] = tile_cost(b->items[i].fwd);
-    icost[i] = tile_cost(b->items[i].inv);
+  b->runs.reserve(2 * size_t(b->count));
+  std::vector<std::pair<int64_t, int>> order(b->count);  // cost, item
+  int64_t first = 0;
+  for (const auto plan : {&BatchItem::fwd, &BatchItem::inv}) {
+    for (uint32_t i = 0; i < b->count; ++i) order[i] = {tile_cost(b->items[i].*plan), int(i)};
+    std::stable_sort(order.begin(), order.end(),
+                     [](const auto &x, const auto &y) { return x.first > y.first; });
+    for (const auto &o : order) {
+      b->runs.push_back({first, o.second, 0});
+      first += (b->items[o.second].*plan).n_waves;
+    }
   }
-  std::stable_sort(ft.begin(), ft.end(), [&](const int2 &x, const int2 &y) { return fcost[x.x] > fcost[y.x]; });
-  std::stable_sort(it.begin(), it.end(), [&](const int2 &x, const int2 &y) { return icost[x.x] > icost[y.x]; });
-  if (ft.size() + it.size() > 0x7fffffffull) {
-    delete b;
+}
+
+}  // namespace
+
+extern "C" {
+
+int dwtfrag_batch_create(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_entry *tune,
+                         uint32_t n_tune, dwtfrag_batch **out) {
+  if (!out) return DWTFRAG_EINVAL;
+  *out = nullptr;
+  if (!items || count == 0 || count > (1u << 30) || (n_tune && !tune)) return DWTFRAG_EINVAL;
+  std::unique_ptr<dwtfrag_batch> b(new (std::nothrow) dwtfrag_batch());
+  if (!b) return DWTFRAG_ERANGE;
+  try {
+    const int rc = plan_items(items, count, tune, n_tune, b.get());
+    if (rc != DWTFRAG_OK) return rc;
+    plan_queues(b.get());
+  } catch (const std::bad_alloc &) {  // tables larger than the host's memory
     return DWTFRAG_ERANGE;
   }
-  b->n_fwd = int64_t(ft.size());
-  b->n_inv = int64_t(it.size());
-  b->tiles = std::move(ft);
-  b->tiles.insert(b->tiles.end(), it.begin(), it.end());
   b->fwd_blocks = persistent_blocks(fwd_batch_blocks_per_cu());
   b->inv_blocks = persistent_blocks(inv_batch_blocks_per_cu());
   b->off_ctr = 0;
   b->off_items = a256(2 * sizeof(BatchCounters));
-  b->off_tiles = a256(b->off_items + count * sizeof(BatchItem));
-  b->bytes = a256(b->off_tiles + b->tiles.size() * sizeof(int2));
-  *out = b;
+  b->off_runs = a256(b->off_items + count * sizeof(BatchItem));
+  b->off_tiles = a256(b->off_runs + b->runs.size() * sizeof(BatchRun));
+  b->bytes = a256(b->off_tiles + uint64_t(b->n_fwd + b->n_inv) * sizeof(int2));
+  *out = b.release();
   return DWTFRAG_OK;
 }
 
@@ -165,20 +182,21 @@ int dwtfrag_batch_upload(dwtfrag_batch *b, void *device_plan, uint64_t device_by
   if (device_bytes < b->bytes) return DWTFRAG_EWORKSPACE;
   char *dev = static_cast<char *>(device_plan);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // The copies run asynchronously on the stream: their sources (the zero
-  // counters below, the plan's own tables) stay in place until
-  // dwtfrag_batch_destroy, which waits for the event recorded behind them.
-  // The queue counters start at zero (the kernels leave them at zero).
-  static const BatchCounters zero[2] = {};
-  if (hipMemcpyAsync(dev + b->off_ctr, zero, sizeof(zero), hipMemcpyHostToDevice, st) != hipSuccess)
-    return DWTFRAG_EDEVICE;
+  // The copies run asynchronously on the stream: their sources (the plan's own
+  // tables) stay in place until dwtfrag_batch_destroy, which waits for the
+  // event recorded behind them.
   if (hipMemcpyAsync(dev + b->off_items, b->items.data(), b->items.size() * sizeof(BatchItem),
                      hipMemcpyHostToDevice, st) != hipSuccess)
     return DWTFRAG_EDEVICE;
-  if (!b->tiles.empty() &&
-      hipMemcpyAsync(dev + b->off_tiles, b->tiles.data(), b->tiles.size() * sizeof(int2),
+  if (hipMemcpyAsync(dev + b->off_runs, b->runs.data(), b->runs.size() * sizeof(BatchRun),
                      hipMemcpyHostToDevice, st) != hipSuccess)
     return DWTFRAG_EDEVICE;
+  const int64_t n_tiles = b->n_fwd + b->n_inv;
+  hipLaunchKernelGGL(batch_tiles_kernel, dim3(unsigned((n_tiles + 255) / 256)), dim3(256), 0, st,
+                     reinterpret_cast<const BatchRun *>(dev + b->off_runs), int64_t(b->runs.size()),
+                     reinterpret_cast<int2 *>(dev + b->off_tiles), n_tiles,
+                     reinterpret_cast<BatchCounters *>(dev + b->off_ctr));
+  if (hipGetLastError() != hipSuccess) return DWTFRAG_EDEVICE;
   if (!b->uploaded && hipEventCreateWithFlags(&b->uploaded, hipEventDisableTiming) != hipSuccess) {
     b->uploaded = nullptr;
     return DWTFRAG_EDEVICE;
