@@ -810,7 +810,7 @@ def run_batch(args):
     t0 = time.time()
     tune = {}
     if not args.no_tune:
-        tune = B.tune_classes(xs, widths, levels)
+        tune = B.tune_classes(xs, widths, levels, candidates=B.TILE_SHAPES)
         log(f"tuned {len(tune)} classes in {time.time() - t0:.1f}s: "
             + ", ".join(f"{k}->({v.seg_rows},{v.lane_cols})" for k, v in sorted(tune.items())))
     b = B.Batch(xs, widths, levels, keys, nonces, tune=tune)

@@ -84,11 +84,16 @@ typedef struct {
 
 /* Optional launch shape (0 in a field = library default).  Results do not
  * depend on it; it only trades parallelism against halo recomputation.  The
- * default cuts the rows into as many segments as the device keeps wavefronts
- * resident for that kernel (one round), at least two 2^levels-row units each. */
+ * default is a segment height by depth and size: short where the wavefronts
+ * are few, up to 24 to 96 rows where they are many. */
 typedef struct {
   uint32_t seg_rows;        /* rows per segment (rounded up to 2^levels; segments are
-                               balanced to within 2^levels rows) */
+                               balanced to within 2^levels rows).  A wavefront keeps its
+                               segment's keystream, so that the rows are at most 32, 64,
+                               128 at one, two, three levels of 8 columns per lane, 16,
+                               64, 128, 128 at one to four levels of 16; more is taken as
+                               that, and too few for one launch of a very tall view as
+                               that too. */
   uint32_t lane_cols;       /* columns per lane at level 1: 8 or 16 (16 needed for 4 levels) */
 } dwtfrag_launch;
 
@@ -220,9 +225,9 @@ int dwtfrag_batch_restore(const dwtfrag_batch *plan, void *stream);
 void dwtfrag_batch_destroy(dwtfrag_batch *plan);
 
 /* Autotuner: time protect + restore of one buffer (device `in`, n bytes)
- * under each candidate launch shape (rows per tile 0 = the single-buffer
- * default, 64, 128, 256; 8 and 16 columns per lane where the levels allow),
- * `trials` times each, with HIP events on `stream`, and return the fastest in
+ * under each candidate launch shape (the default; 8, 16, 24, 32, 48, 64, 96
+ * and 128 rows per segment, those that the depth allows; 8 and 16 columns per
+ * lane where it allows both), `trials` times each, with HIP events on `stream`, and return the fastest in
  * *best (and its time in microseconds in *best_us).  `scratch` (device) holds
  * the fragments, the output and the workspace: at least
  * geom.priv_bytes + geom.pub_bytes + n + geom.workspace_bytes + 768 bytes,

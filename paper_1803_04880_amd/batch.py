@@ -45,17 +45,39 @@ def autotune(x: torch.Tensor, width: int, levels: int, trials: int = 3, stream=N
     return best, float(us.value)
 
 
+# Candidates for ``tune_classes`` over all that the kernels have: the default
+# (48 rows, 16 at one level), and shorter and taller tiles.
+TILE_SHAPES = ((0, 16), (24, 16), (32, 16), (64, 16), (96, 16), (128, 16))
+# The tallest tile of each depth (the keystream that a wavefront keeps); a
+# taller one is taken as that.
+MAX_TILE_ROWS = {1: 16, 2: 64, 3: 128, 4: 128}
+
+
+def tile_rows(rows: int, levels: int) -> int:
+    """Rows of the tiles that a batch has where ``rows`` are asked for."""
+    unit = 1 << levels
+    return min(-(-(rows or 48) // unit) * unit, MAX_TILE_ROWS[levels])
+
+
 def tune_classes(buffers, widths, levels, trials: int = 2,
                  candidates=((64, 16), (128, 16), (256, 16)), stream=None):
     """Batch autotuner: for every (width, levels) class of the buffers, time a
     batched protect + restore of that class's buffers under each candidate
     tile shape (rows per tile, columns per lane; batch tiles always have 16
-    columns per lane) with HIP events and keep the fastest.  Returns
-    {(width, levels): Launch} for ``Batch(tune=...)``.
+    columns per lane) with HIP events and keep the fastest.  Of candidates
+    that give the same tiles at a depth (``tile_rows``) the first is timed.
+    Returns {(width, levels): Launch} for ``Batch(tune=...)``.
 
     Unlike ``autotune`` (one buffer alone, where finer tiles fill the device),
-    this times the shapes where they will run: many buffers per launch, where
-    coarser tiles save halo work."""
+    this times the shapes where they will run: many buffers per launch.  The
+    default candidates are tall tiles only, which pay for many small buffers
+    (400 of 256 KiB at three levels: 285 us at 48 rows, 242 at 128);
+    ``candidates=TILE_SHAPES`` searches the whole range, so that no class by
+    itself loses against the default (100 of 2.9 MB of width 1733 at two
+    levels: 711 us at 24 rows, 747 at 48, 792 at 64).  A class of few buffers
+    is timed short of work and prefers short tiles; in a batch of many classes
+    that fill the device together the default is as good (2048 uneven buffers:
+    694 GB/s, tuned 688)."""
     groups = {}
     for i, (w, lv) in enumerate(zip(widths, levels)):
         groups.setdefault((w, lv), []).append(i)
@@ -64,7 +86,11 @@ def tune_classes(buffers, widths, levels, trials: int = 2,
     for key, idx in groups.items():
         xs = [buffers[i] for i in idx]
         best = None
+        seen = set()
         for rows, cols in candidates:
+            if tile_rows(rows, key[1]) in seen:
+                continue
+            seen.add(tile_rows(rows, key[1]))
             b = Batch(xs, [key[0]] * len(xs), [key[1]] * len(xs), [bytes(16)] * len(xs),
                       [bytes(16)] * len(xs), tune={key: (rows, cols)})
             b.protect(stream=st)

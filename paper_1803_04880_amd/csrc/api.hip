@@ -154,6 +154,16 @@ int inv_seg_rows(int L, int C1, int n_win, int W, int H) {
 // / 1388, 96: 1378 / 1417; as single launches' 1562 / 1372.
 constexpr int kBatchRows = 48;
 
+// Whether a stage runs at 16 columns a lane by default: 8 but 16 (the per-row
+// work spread over twice the columns) for a forward of three levels and 128 Mi
+// elements (176 against 181 us at 256 MiB; 46.2 against 46.9 at 64 MiB, and one
+// and two levels are as fast at 8: 228, 168 against 227, 169).  The inverse at
+// 16 is slower at all sizes (256 MiB at one, two and three levels 268, 166, 161
+// against 253, 162, 158 us).  Four levels need 16 columns.
+bool wide_stage(bool forward, int L, uint64_t cells) {
+  return L == 4 || (forward && L == 3 && cells >= (uint64_t(1) << 27));
+}
+
 // Fill stage s's parameters.  forward selects the halo shape of the direction;
 // alone: the stage runs as its own launch (not as one item of a batch that
 // shares the device).
@@ -162,15 +172,8 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   std::memset(P, 0, sizeof(*P));
   const int lv0 = kMaxFused * s;  // global level of the stage input
   const int L = int(std::min<uint32_t>(kMaxFused, g.levels - lv0));
-  // Default columns per lane: 8, but 16 (the per-row work spread over twice
-  // the columns) for a forward of three levels and 128 Mi elements (176
-  // against 181 us at 256 MiB; 46.2 against 46.9 at 64 MiB, and one and two
-  // levels are as fast at 8: 228, 168 against 227, 169).  The inverse at 16
-  // is slower at all sizes (256 MiB at one, two and three levels 268, 166,
-  // 161 against 253, 162, 158 us).  Four levels need 16 columns.
   const uint64_t cells = uint64_t(g.h[lv0]) * g.w[lv0];
-  const bool wide = forward && L == 3 && cells >= (uint64_t(1) << 27);
-  int C1 = (launch && launch->lane_cols) ? int(launch->lane_cols) : (wide ? 16 : 8);
+  int C1 = (launch && launch->lane_cols) ? int(launch->lane_cols) : wide_stage(forward, L, cells) ? 16 : 8;
   if (C1 != 8 && C1 != 16) return DWTFRAG_EINVAL;
   if (L == 4) C1 = 16;
   // (a launch of more than 2^30 rows: 16 columns' segments would be too many)
@@ -435,12 +438,23 @@ int dwtfrag_autotune(const uint8_t *in, uint64_t n, uint32_t width, uint32_t lev
   }
   float best_t = -1.0f;
   dwtfrag_launch best_l{0, 0};
-  const uint32_t rows[] = {0, 64, 128, 256};
-  const uint32_t cols[] = {8, 16};
+  // The default, and the heights that the kernels have: multiples of the first
+  // stage's unit, up to the rows whose keystream a wavefront keeps, and no more
+  // than one past the view's.  (Columns 0: the default of a stage whose
+  // directions differ; elsewhere it is one of the others.)
+  const int L0 = int(std::min<uint32_t>(kMaxFused, levels));
+  const uint32_t rows[] = {0, 8, 16, 24, 32, 48, 64, 96, 128};
+  const uint32_t cols[] = {0, 8, 16};
+  const uint64_t cells = g.h[0] * g.w[0];
   rc = DWTFRAG_OK;
   for (uint32_t c : cols) {
+    if (c == 0 && wide_stage(true, L0, cells) == wide_stage(false, L0, cells)) continue;
     if (levels % kMaxFused == 0 && c == 8) continue;  // a four-level stage needs 16 columns
+    uint64_t tallest = 0;
     for (uint32_t r : rows) {
+      if (r && (c == 0 || r % (1u << L0) || int(r) > fwd_max_rows(L0, L0 == 4 ? 16 : int(c)) || tallest >= g.h[0]))
+        continue;
+      tallest = r;
       const dwtfrag_launch ln{r, c};
       // one untimed pair, then `trials` timed pairs; the first failing call's
       // code is returned
