@@ -88,9 +88,10 @@ def tune_classes(buffers, widths, levels, trials: int = 2,
         best = None
         seen = set()
         for rows, cols in candidates:
-            if tile_rows(rows, key[1]) in seen:
+            shape = tile_rows(rows, key[1]) if key[1] in MAX_TILE_ROWS else rows
+            if shape in seen:
                 continue
-            seen.add(tile_rows(rows, key[1]))
+            seen.add(shape)
             b = Batch(xs, [key[0]] * len(xs), [key[1]] * len(xs), [bytes(16)] * len(xs),
                       [bytes(16)] * len(xs), tune={key: (rows, cols)})
             b.protect(stream=st)

@@ -97,3 +97,11 @@ def test_learned_column_of_more_tiles_than_a_grid_takes_at_8_wavefronts():
     print(f"n={n} width=1 learned", flush=True)
     priv, pub = learned.protect(x, 1, 1, bytes(16), bytes(16), net)
     assert torch.equal(learned.restore(priv, pub, n, 1, 1, bytes(16), bytes(16), net), x)
+
+
+@pytest.mark.parametrize("levels", [0, 5, -1])
+def test_tuning_a_depth_that_batches_do_not_have_is_refused(levels):
+    from paper_1803_04880_amd import batch
+    x = torch.zeros(1000, dtype=torch.uint8, device=DEV)
+    with pytest.raises(dwtfrag.DwtfragError):
+        batch.tune_classes([x], [32], [levels], trials=1)
