@@ -3,6 +3,7 @@
 #include "dwtfrag.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <mutex>
 
@@ -46,6 +47,19 @@ void expand_key(const uint8_t key[16], const uint8_t nonce[16], AesKey *out) {
   }
   out->nonce_hi = hi;
   out->nonce_lo = lo;
+}
+
+// Asked once per device; 256 where the query fails (no device: planning only).
+int device_cus() {
+  constexpr int kDev = 64;
+  static std::atomic<int> cache[kDev];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDev) return 256;
+  int cus = cache[dev].load(std::memory_order_relaxed);
+  if (cus > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  cache[dev].store(cus, std::memory_order_relaxed);
+  return cus;
 }
 
 namespace {
@@ -117,9 +131,10 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 // Rows of a forward segment.  A segment recomputes 2^(L+1) + 2^L - 3 rows, so
 // taller is less work, but every wavefront is one serial stream: a launch of
-// its own wants about 940 of them (at one level, where the cipher counts
-// most, 1536) before its segments grow past one unit.  The tallest worth it,
-// by level (measured, us at 4096 columns, 16 / 64 MiB, or 32768, 256 MiB):
+// its own wants about 940 of them on 256 compute units (at one level, where
+// the cipher counts most, 1536) before its segments grow past one unit.  The
+// tallest worth it, by level (measured, us at 4096 columns, 16 / 64 MiB, or
+// 32768, 256 MiB):
 //   1: 24 rows 24.9 / 68.6 / 228 (8: 25.0 / 67.9 / 252);
 //   2: 16 rows 16.6 / 44.8 / 179, 32: 19.5 / 46.7 / 168;
 //   3: 96 rows (8 columns a lane) 46.9 at 64 MiB, 48: 47.7, 16: 56.2; at 16
@@ -128,21 +143,21 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells) {
   const bool large = cells >= (uint64_t(1) << 27);
   const int most = L == 1 ? 24 : L == 2 ? (large ? 32 : 16) : L == 3 ? (C1 == 16 ? 24 : 96) : large ? 64 : 96;
-  const int64_t want = int64_t(n_win) * H / (L == 1 ? 1536 : 940);
+  const int64_t want = int64_t(n_win) * H * 256 / (int64_t(L == 1 ? 1536 : 940) * device_cus());
   const int rows = round_up(int(std::min<int64_t>(std::max<int64_t>(want, 1), most)), 1 << L);
   return std::min(rows, fwd_max_rows(L, C1));
 }
 
 // Rows of an inverse segment: the least that make no more than two wavefronts
-// for each of the 1024 SIMDs (four where the row's end cuts a lane's columns:
-// those wavefronts take 2.5 times as long a row), up to 32 rows (at four
-// levels 48).  Measured, us: 16 MiB of width 4096 at three levels 24 rows
+// for each SIMD, of which a compute unit has four (four wavefronts where the
+// row's end cuts a lane's columns: those take 2.5 times as long a row), up to
+// 32 rows (at four levels 48).  Measured on 256 units, us: 16 MiB of width 4096 at three levels 24 rows
 // 17.7, 16: 19.0, 32: 20.0; 12 MB of width 3001 at two levels 8 rows 23.9,
 // 16: 26.4, 32: 32.3; 256 MiB at three levels 32 rows 161, 24: 162, 48: 163,
 // 16: 176; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
 int inv_seg_rows(int L, int C1, int n_win, int W, int H) {
   const int unit = 1 << L, most = std::min(L == 4 ? 48 : 32, inv_max_rows(L, C1));
-  const int64_t waves = W % C1 ? 4096 : 2048;
+  const int64_t waves = int64_t(W % C1 ? 16 : 8) * device_cus();
   int rows = unit;
   while (rows < most && int64_t(n_win) * ((H + rows - 1) / rows) > waves) rows += unit;
   return std::min(rows, most);

@@ -229,10 +229,14 @@ constexpr int inv_max_rows(int L, int C1) { return fwd_max_rows(L, C1); }
 constexpr int inv_ks_words(int L, int C1) {
   return ((fwd_ll_rows(L, C1) + 2) * (64 * C1 / (8 << L) + 2) + 1) * 4;
 }
-// Wavefronts per workgroup of a launch: one where the whole grid is
-// about a wavefront per compute unit (each then has an LDS of its own for
+// Wavefronts per workgroup of a launch: one where the whole grid is no more
+// than two wavefronts per compute unit (each then has an LDS of its own for
 // the AES lookups), else four.
-constexpr int block_waves(int n_waves) { return n_waves <= 512 ? 1 : kWavesPerBlock; }
+constexpr int block_waves(int n_waves, int cus) { return n_waves <= 2 * cus ? 1 : kWavesPerBlock; }
+
+// Compute units of the current device (a partition has fewer than the 256 that
+// the constants of the launch rules were measured on: they go with it).
+int device_cus();
 
 // Most wavefronts of a launch: HIP takes fewer than 2^32 work-items per grid
 // dimension (with the last workgroup's idle wavefronts counted).  Segments of

@@ -844,7 +844,10 @@ __global__ __launch_bounds__(64 * NW) void linv_level_kernel(LvCoef src, Dst dst
 // Sixteen streams of such images, protect / restore of 64: 4 / 4 / 4 wavefronts
 // 4.64 / 5.58 ms, these 4.78 / 5.37, the inverse's 256 tiles at 16 5.67.
 template <int N> struct Waves { static constexpr int value = N; };
-inline int fwd_level_waves(int64_t tiles) { return tiles <= 512 ? 16 : tiles <= 2048 ? 8 : 4; }
+inline int fwd_level_waves(int64_t tiles) {
+  const int cus = device_cus();
+  return tiles <= 2 * cus ? 16 : tiles <= 8 * cus ? 8 : 4;
+}
 // (8 where the launch has fewer than the 2^32 work-items that HIP takes)
 inline int inv_level_waves(int64_t tiles) { return tiles < (int64_t(1) << 23) ? 8 : 4; }
 

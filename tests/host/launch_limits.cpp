@@ -16,7 +16,7 @@ static const char *what = "";
 
 static hipError_t planned(int L, int C1, const dwtfrag::StageParams &P) {
   using namespace dwtfrag;
-  const int per = block_waves(P.n_waves);
+  const int per = block_waves(P.n_waves, 256);
   const uint64_t threads = (uint64_t(P.n_waves) + per - 1) / per * per * 64;
   const int64_t most_units = (int64_t(P.units) + P.n_seg - 1) / P.n_seg;
   const bool ok = P.n_waves > 0 && P.n_waves == int64_t(P.n_win) * P.n_seg && threads < (uint64_t(1) << 32) &&
