@@ -8,9 +8,8 @@ hipError_t launch_fwd_tail(int L, int C1, const void *in, int16_t *pub, int16_t 
 
 hipError_t launch_fwd(int L, int C1, bool u8in, const void *in, int16_t *pub, int16_t *llout,
                       const StageParams &P, hipStream_t s) {
-  // (four levels, where the checks for a partial row spill registers, and
-  // int16 stages, which are whole, have no such kernels)
-  if (L < 4 && P.n_valid < int64_t(P.H) * P.W) return launch_fwd_tail(L, C1, in, pub, llout, P, s);
+  // (int16 stages are whole)
+  if (P.n_valid < int64_t(P.H) * P.W) return launch_fwd_tail(L, C1, in, pub, llout, P, s);
 #define DWTFRAG_CASE(LL, CC)                                                           \
   if (L == LL && C1 == CC)                                                             \
     return u8in ? launch_fwd_t<LL, CC, true, false>(in, pub, llout, P, s)                     \

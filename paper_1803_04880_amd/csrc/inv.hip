@@ -8,9 +8,8 @@ hipError_t launch_inv_tail(int L, int C1, const int16_t *llin, const int16_t *pu
 
 hipError_t launch_inv(int L, int C1, bool u8out, const int16_t *llin, const int16_t *pub,
                       void *out, const StageParams &P, hipStream_t s) {
-  // (four levels, where the checks for a partial row spill registers, and
-  // int16 stages, which are whole, have no such kernels)
-  if (L < 4 && P.n_valid < int64_t(P.H) * P.W) return launch_inv_tail(L, C1, llin, pub, out, P, s);
+  // (int16 stages are whole)
+  if (P.n_valid < int64_t(P.H) * P.W) return launch_inv_tail(L, C1, llin, pub, out, P, s);
 #define DWTFRAG_CASE(LL, CC)                                                   \
   if (L == LL && C1 == CC)                                                     \
     return u8out ? launch_inv_t<LL, CC, true, false>(llin, pub, out, P, s)            \
