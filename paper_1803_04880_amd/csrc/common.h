@@ -263,6 +263,21 @@ __host__ __device__ constexpr int read_shift(int c0, int last, int span) {
   return past < span ? past : span;
 }
 
+// Whether a view goes to the kernels of few rows, which loop over the rows
+// there are, where the streaming kernel takes two whole units of 2^L rows: up
+// to half a unit, and up to a whole one where the stream's last window or
+// segment is of the slower kind (lanes cut by the row's end; forward, a partial
+// last row).  One LL row in any case.  Measured, us forward / inverse, few rows
+// against the stream: four levels of width 4096, 1 row 8 / 8 against 17 / 34,
+// 8 rows 12 / 12 against 17 / 35 (16 rows: the stream 17 / 15); of width 4099,
+// 1 row 8 / 10 against 37 / 35, 16 rows 18 / 27 against 37 / 36; three levels
+// of width 4099, 8 rows 9 / 13 against 14 / 16; 12 rows of 1 MiB less a third,
+// four levels, 20 / 35 against 27 / 26.
+inline bool few_rows(const StageParams &P, int L, int C1, bool forward) {
+  const bool slow = P.W % C1 != 0 || (forward && P.n_valid < int64_t(P.H) * P.W);
+  return P.hdim[slow ? L : L - 1] == 1;
+}
+
 // First level-0 row of segment s (s == n_seg gives units * unit_rows).
 template <class SP> __device__ __forceinline__ int seg_start(SP &P, int s) {
   return P.unit_rows * int((int64_t(s) * P.units) / P.n_seg);

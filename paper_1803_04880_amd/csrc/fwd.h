@@ -419,14 +419,7 @@ struct FwdWave {
           // keystream bytes of this lane's elements of LL row k (a row's
           // first block starts up to 14 bytes before its first element)
           const int at = (k - (B.Y0 >> L)) * 16 * ks_nb + (2 * (k * (wl & 7) + ks_c0) & 15);
-          typedef uint32_t u32_h __attribute__((aligned(2)));
-          const char *p = reinterpret_cast<const char *>(ks) + (has_low ? at : 0) + ks_off;
-          if constexpr (M<L> == 1) {
-            out[0] ^= *reinterpret_cast<const uint16_t *>(p);
-          } else {
-#pragma unroll
-            for (int j = 0; j < Np; ++j) out[j] ^= reinterpret_cast<const u32_h *>(p)[j];
-          }
+          encrypt(out, has_low ? at : 0);
         }
         store_row<l>(pLL, has_low, wl, out);
       }
@@ -434,6 +427,19 @@ struct FwdWave {
     pLH[l] = uniform_ptr(pLH[l] + 2 * int64_t(wl));
     pHL[l] = uniform_ptr(pHL[l] + 2 * int64_t(wh));
     if constexpr (l == L) pLL = uniform_ptr(pLL + 2 * int64_t(wl));
+  }
+
+  // XORs this lane's LL elements with the keystream of the row that begins at
+  // byte `at`.
+  __device__ __forceinline__ void encrypt(uint32_t (&out)[NP<L>], int at) const {
+    typedef uint32_t u32_h __attribute__((aligned(2)));
+    const char *p = reinterpret_cast<const char *>(ks) + at + ks_off;
+    if constexpr (M<L> == 1) {
+      out[0] ^= *reinterpret_cast<const uint16_t *>(p);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NP<L>; ++j) out[j] ^= reinterpret_cast<const u32_h *>(p)[j];
+    }
   }
 
   template <int S, bool CHK> __device__ __forceinline__ void unit(int v, int v1) {

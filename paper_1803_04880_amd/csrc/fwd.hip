@@ -6,8 +6,12 @@ namespace dwtfrag {
 hipError_t launch_fwd_tail(int L, int C1, const void *in, int16_t *pub, int16_t *llout,
                            const StageParams &P, hipStream_t s);
 
+hipError_t launch_fwd_few(int L, int C1, bool u8in, const void *in, int16_t *pub, int16_t *llout,
+                          const StageParams &P, hipStream_t s);
+
 hipError_t launch_fwd(int L, int C1, bool u8in, const void *in, int16_t *pub, int16_t *llout,
                       const StageParams &P, hipStream_t s) {
+  if (few_rows(P, L, C1, true)) return launch_fwd_few(L, C1, u8in, in, pub, llout, P, s);
   // (int16 stages are whole)
   if (P.n_valid < int64_t(P.H) * P.W) return launch_fwd_tail(L, C1, in, pub, llout, P, s);
 #define DWTFRAG_CASE(LL, CC)                                                           \
