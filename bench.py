@@ -71,8 +71,8 @@ def percentile(xs, q):
 # sources of the kernels and launch planning the plain protect / restore runs
 PLAIN_PATH_SOURCES = ("api.hip", "common.h", "fwd.h", "fwd.hip", "fwd_kernel.h", "inv.h", "inv.hip",
                       "inv_kernel.h", "lift.h", "pack.h")
-BATCH_PATH_SOURCES = PLAIN_PATH_SOURCES + ("batch.h", "batch.hip", "fwd_batch.hip",
-                                             "inv_batch.hip")
+BATCH_PATH_SOURCES = PLAIN_PATH_SOURCES + ("batch.h", "batch.hip", "fwd_batch_kernel.h",
+                                             "inv_batch_kernel.h")
 
 
 def source_hash(sources=PLAIN_PATH_SOURCES) -> str:

@@ -13,9 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdwtfrag.so")
-SOURCES = ["api.hip", "batch.hip", "fwd.hip", "fwd_few.hip", "fwd_tail.hip", "fwd_batch.hip", "inv.hip",
-           "inv_few.hip", "inv_tail.hip", "inv_batch.hip", "ctr.hip", "learned.hip", "se8.hip",
-           "refstream.hip"]
+SOURCES = ["api.hip", "batch.hip", "fwd.hip", "fwd_few.hip", "fwd_tail.hip", "fwd_batch.hip",
+           "fwd_batch_tail.hip", "inv.hip", "inv_few.hip", "inv_tail.hip", "inv_batch.hip",
+           "inv_batch_tail.hip", "ctr.hip", "learned.hip", "se8.hip", "refstream.hip"]
 ARCH = os.environ.get("DWTFRAG_ARCH", "gfx950")
 # Per-source compiler options: the SHA-2 compressions of se8.hip are fully
 # unrolled loops (their message schedule lives in registers only when every

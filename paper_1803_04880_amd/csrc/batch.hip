@@ -28,6 +28,12 @@ hipError_t launch_fwd_batch(const BatchItem *items, const int2 *tiles, int64_t n
                             BatchCounters *ctr, int blocks, hipStream_t s);
 hipError_t launch_inv_batch(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
                             BatchCounters *ctr, int blocks, hipStream_t s);
+// The kernels of batches with partial last rows (weak: a build of the planner
+// alone for the host has none).
+__attribute__((weak)) hipError_t launch_fwd_batch_tail(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
+                                                       BatchCounters *ctr, int blocks, hipStream_t s);
+__attribute__((weak)) hipError_t launch_inv_batch_tail(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
+                                                       BatchCounters *ctr, int blocks, hipStream_t s);
 int fwd_batch_blocks_per_cu();
 int inv_batch_blocks_per_cu();
 int plan_single_stage(uint64_t n, uint32_t width, uint32_t levels, bool forward,
@@ -53,6 +59,7 @@ struct dwtfrag_batch {
   std::vector<BatchItem> items;
   std::vector<BatchRun> runs;              // forward queue, then inverse queue
   int64_t n_fwd = 0, n_inv = 0;            // tiles per direction
+  int64_t part_fwd = 0, part_inv = 0;      // of them with a partial last row
   int fwd_blocks = 0, inv_blocks = 0;      // persistent grid per direction
   uint64_t off_ctr = 0, off_items = 0, off_runs = 0, off_tiles = 0, bytes = 0;
   char *dev = nullptr;                     // caller's device copy, set by upload
@@ -77,6 +84,19 @@ int persistent_blocks(int per_cu) {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     cus = 256;
   return cus * std::max(1, per_cu);
+}
+
+// Whether a drain runs the kernel whose plain form takes partial last rows.
+// The other one runs their tiles in its general form, twice as long a row, at
+// the end of a short drain as long again as the drain; this one's checks cost
+// every other tile of whole lanes 3 to 20 %.  A few rounds of tiles, where the
+// longest tile counts: 30 buffers of 4 to 256 KiB forward / inverse 75 / 91 ->
+// 44 / 46 us; longer drains by the share of such tiles: 256 buffers up to 16
+// MiB (2 %) 560 / 580 -> 530 / 584, up to 64 MiB (1 %) 1557 / 1595 -> 1522 /
+// 1685; 1000 of 100 rows of 4096 (a third of the tiles), four levels, 455 / 561
+// -> 405 / 479, and whole 405 / 404 -> 432 / 481.
+bool partial_rows_kernel(int64_t part, int64_t tiles, int blocks, int share) {
+  return part > 0 && (tiles <= 4 * kWavesPerBlock * int64_t(blocks) || part * share > tiles);
 }
 
 // Every item's plans and buffers, and the tiles of each direction counted.
@@ -111,6 +131,10 @@ int plan_items(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_ent
     bi.out = src.out;
     bi.priv_bytes = priv_bytes;
     bi.levels = int32_t(src.levels);
+    if (src.n % src.width) {
+      b->part_fwd += bi.fwd.n_win;
+      b->part_inv += bi.inv.n_win;
+    }
     b->n_fwd += bi.fwd.n_waves;
     b->n_inv += bi.inv.n_waves;
     if (b->n_fwd + b->n_inv > 0x7fffffffll) return DWTFRAG_ERANGE;
@@ -213,7 +237,9 @@ int dwtfrag_batch_protect(const dwtfrag_batch *b, void *stream) {
   const BatchItem *items = reinterpret_cast<const BatchItem *>(b->dev + b->off_items);
   const int2 *tiles = reinterpret_cast<const int2 *>(b->dev + b->off_tiles);
   const int blocks = int(std::min<int64_t>(b->fwd_blocks, (b->n_fwd + kWavesPerBlock - 1) / kWavesPerBlock));
-  if (launch_fwd_batch(items, tiles, b->n_fwd, ctr, blocks, static_cast<hipStream_t>(stream)) != hipSuccess)
+  const auto launch = launch_fwd_batch_tail && partial_rows_kernel(b->part_fwd, b->n_fwd, b->fwd_blocks, 200)
+                          ? launch_fwd_batch_tail : launch_fwd_batch;
+  if (launch(items, tiles, b->n_fwd, ctr, blocks, static_cast<hipStream_t>(stream)) != hipSuccess)
     return DWTFRAG_EDEVICE;
   return DWTFRAG_OK;
 }
@@ -227,7 +253,9 @@ int dwtfrag_batch_restore(const dwtfrag_batch *b, void *stream) {
   const BatchItem *items = reinterpret_cast<const BatchItem *>(b->dev + b->off_items);
   const int2 *tiles = reinterpret_cast<const int2 *>(b->dev + b->off_tiles) + b->n_fwd;
   const int blocks = int(std::min<int64_t>(b->inv_blocks, (b->n_inv + kWavesPerBlock - 1) / kWavesPerBlock));
-  if (launch_inv_batch(items, tiles, b->n_inv, ctr, blocks, static_cast<hipStream_t>(stream)) != hipSuccess)
+  const auto launch = launch_inv_batch_tail && partial_rows_kernel(b->part_inv, b->n_inv, b->inv_blocks, 20)
+                          ? launch_inv_batch_tail : launch_inv_batch;
+  if (launch(items, tiles, b->n_inv, ctr, blocks, static_cast<hipStream_t>(stream)) != hipSuccess)
     return DWTFRAG_EDEVICE;
   return DWTFRAG_OK;
 }

@@ -1,65 +1,17 @@
-// Inverse launch of a batch (the streaming code is in inv.h).
-#include "batch.h"
-#include "inv.h"
+// Inverse launch of a batch.
+#include "inv_batch_kernel.h"
 
 namespace dwtfrag {
 
-// One persistent launch drains the batch's tile queue; each tile is one
-// wavefront rectangle of one item (the item's own plan, buffers and keys),
-// run by the streaming code of the item's depth.
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int kInvBatchKs = cmax(cmax(inv_ks_words(1, kBatchCols), inv_ks_words(2, kBatchCols)),
-                                 cmax(inv_ks_words(3, kBatchCols), inv_ks_words(4, kBatchCols)));
-
-template <int L>
-__device__ __forceinline__ void inv_batch_tile(ConstItem &it, int wave, uint32_t *ks,
-                                               const uint32_t *te, const uint32_t *kw, int lane) {
-  inv_rect<L, kBatchCols, true, false>(it.inv, wave, reinterpret_cast<const int16_t *>(it.priv), it.pub,
-                                it.out, ks, te, kw, lane, [] {});
-}
-
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(3)))
-void inv_batch_kernel(const BatchItem *__restrict__ items, const int2 *__restrict__ tiles,
-                      int64_t n_tiles, BatchCounters *__restrict__ ctr) {
-  __shared__ uint32_t s_ks[kWavesPerBlock][kInvBatchKs];
-  __shared__ uint32_t s_te[1024];
-  __shared__ uint32_t s_kw[kWavesPerBlock][kKeyWords];
-  load_aes_te(s_te);
-  __syncthreads();
-  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  for (;;) {
-    unsigned int t = 0;
-    if (lane == 0) t = atomicAdd(&ctr->head, 1u);
-    t = __builtin_amdgcn_readfirstlane(t);
-    if (int64_t(t) >= n_tiles) break;
-    const int2 e = tiles[t];
-    const int wave = __builtin_amdgcn_readfirstlane(e.y);
-    ConstItem &it = const_items(items)[__builtin_amdgcn_readfirstlane(e.x)];
-    if (lane < kKeyWords) s_kw[wib][lane] = key_word(it.inv.key, lane);  // this item's keys
-    wave_lds_sync();
-    switch (it.levels) {
-      case 1: inv_batch_tile<1>(it, wave, s_ks[wib], s_te, s_kw[wib], lane); break;
-      case 2: inv_batch_tile<2>(it, wave, s_ks[wib], s_te, s_kw[wib], lane); break;
-      case 3: inv_batch_tile<3>(it, wave, s_ks[wib], s_te, s_kw[wib], lane); break;
-      default: inv_batch_tile<4>(it, wave, s_ks[wib], s_te, s_kw[wib], lane); break;
-    }
-    wave_lds_sync();
-  }
-  batch_finish(ctr);
-}
-
 hipError_t launch_inv_batch(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
                             BatchCounters *ctr, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(inv_batch_kernel, dim3(blocks), dim3(kBlockThreads), 0, s, items, tiles,
-                     n_tiles, ctr);
-  return hipGetLastError();
+  return launch_inv_batch_t<false>(items, tiles, n_tiles, ctr, blocks, s);
 }
 
 // Resident workgroups per CU of the batch inverse kernel.
 int inv_batch_blocks_per_cu() {
   int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void *>(&inv_batch_kernel),
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void *>(&inv_batch_kernel<false>),
                                                    kBlockThreads, 0) != hipSuccess)
     return 0;
   return blocks;
