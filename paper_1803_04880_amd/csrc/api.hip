@@ -3,7 +3,6 @@
 #include "dwtfrag.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cstring>
 #include <mutex>
 
@@ -49,17 +48,36 @@ void expand_key(const uint8_t key[16], const uint8_t nonce[16], AesKey *out) {
   out->nonce_lo = lo;
 }
 
-// Asked once per device; 256 where the query fails (no device: planning only).
+namespace {
+
+// Compute units of every device, asked once; 256 where a query fails (no
+// device: planning only).
+struct DeviceUnits {
+  static constexpr int kDev = 64;
+  int units[kDev];
+  bool same = true;  // all devices alike: the current one need not be asked for
+  DeviceUnits() {
+    int count = 0;
+    if (hipGetDeviceCount(&count) != hipSuccess) count = 0;
+    for (int d = 0; d < kDev; ++d) {
+      units[d] = 256;
+      int n = 0;
+      if (d < count && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, d) == hipSuccess && n > 0)
+        units[d] = n;
+      if (d < count && units[d] != units[0]) same = false;
+    }
+    if (count > kDev) same = false;
+  }
+};
+
+}  // namespace
+
 int device_cus() {
-  constexpr int kDev = 64;
-  static std::atomic<int> cache[kDev];
+  static const DeviceUnits all;
+  if (all.same) return all.units[0];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDev) return 256;
-  int cus = cache[dev].load(std::memory_order_relaxed);
-  if (cus > 0) return cus;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-  cache[dev].store(cus, std::memory_order_relaxed);
-  return cus;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= DeviceUnits::kDev) return 256;
+  return all.units[dev];
 }
 
 namespace {
@@ -140,10 +158,10 @@ int round_up(int v, int m) { return (v + m - 1) / m * m; }
 //   3: 96 rows (8 columns a lane) 46.9 at 64 MiB, 48: 47.7, 16: 56.2; at 16
 //      columns 24 rows 176 at 256 MiB (32: 182, 96: 208);
 //   4: 96 rows 53.7 at 64 MiB (64: 60.9), 64 rows 198 at 256 MiB (96: 214).
-int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells) {
+int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells, int cus) {
   const bool large = cells >= (uint64_t(1) << 27);
   const int most = L == 1 ? 24 : L == 2 ? (large ? 32 : 16) : L == 3 ? (C1 == 16 ? 24 : 96) : large ? 64 : 96;
-  const int64_t want = int64_t(n_win) * H * 256 / (int64_t(L == 1 ? 1536 : 940) * device_cus());
+  const int64_t want = int64_t(n_win) * H * 256 / (int64_t(L == 1 ? 1536 : 940) * cus);
   const int rows = round_up(int(std::min<int64_t>(std::max<int64_t>(want, 1), most)), 1 << L);
   return std::min(rows, fwd_max_rows(L, C1));
 }
@@ -155,9 +173,9 @@ int fwd_seg_rows(int L, int C1, int n_win, int H, uint64_t cells) {
 // 17.7, 16: 19.0, 32: 20.0; 12 MB of width 3001 at two levels 8 rows 23.9,
 // 16: 26.4, 32: 32.3; 256 MiB at three levels 32 rows 161, 24: 162, 48: 163,
 // 16: 176; 64 MiB at four levels 48 rows 57.3, 32: 58.6, 64: 66.5.
-int inv_seg_rows(int L, int C1, int n_win, int W, int H) {
+int inv_seg_rows(int L, int C1, int n_win, int W, int H, int cus) {
   const int unit = 1 << L, most = std::min(L == 4 ? 48 : 32, inv_max_rows(L, C1));
-  const int64_t waves = int64_t(W % C1 ? 16 : 8) * device_cus();
+  const int64_t waves = int64_t(W % C1 ? 16 : 8) * cus;
   int rows = unit;
   while (rows < most && int64_t(n_win) * ((H + rows - 1) / rows) > waves) rows += unit;
   return std::min(rows, most);
@@ -225,14 +243,14 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
     P->n_win = (P->W + P->own_w - 1) / P->own_w;
   }
   P->halo_l = hl;
-  P->halo_t = forward ? (1 << (L + 1)) : (1 << L);
   P->halo_b = 1 << L;
   const int unit = 1 << L;
   P->unit_rows = unit;
   P->units = (P->H + unit - 1) / unit;
+  const int cus = alone ? device_cus() : 256;
   int rows = !alone    ? kBatchRows
-             : forward ? fwd_seg_rows(L, C1, P->n_win, P->H, cells)
-                       : inv_seg_rows(L, C1, P->n_win, P->W, P->H);
+             : forward ? fwd_seg_rows(L, C1, P->n_win, P->H, cells, cus)
+                       : inv_seg_rows(L, C1, P->n_win, P->W, P->H, cus);
   if (launch && launch->seg_rows)
     rows = std::max(unit, round_up(int(std::min<uint32_t>(launch->seg_rows, uint32_t(P->H))), unit));
   const int most = forward ? fwd_max_rows(L, C1) : inv_max_rows(L, C1);
@@ -243,6 +261,7 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
   const int64_t waves = int64_t(P->n_win) * P->n_seg;
   if (waves > (int64_t(1) << 30)) return DWTFRAG_ERANGE;
   P->n_waves = int32_t(waves);
+  P->block = block_waves(P->n_waves, cus);
   const bool last = (s == g.stages - 1);
   P->use_aes = last ? 1 : 0;
   P->key = key;

@@ -18,6 +18,9 @@ namespace dwtfrag {
 // Columns per lane of every batch tile.
 constexpr int kBatchCols = 16;
 
+// A depth, to pick a kernel's code by.
+template <int L> struct Level { static constexpr int value = L; };
+
 struct BatchItem {
   StageParams fwd;     // forward plan (halo shape of the forward kernel)
   StageParams inv;     // inverse plan

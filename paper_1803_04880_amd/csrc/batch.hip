@@ -34,6 +34,11 @@ __attribute__((weak)) hipError_t launch_fwd_batch_tail(const BatchItem *items, c
                                                        BatchCounters *ctr, int blocks, hipStream_t s);
 __attribute__((weak)) hipError_t launch_inv_batch_tail(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
                                                        BatchCounters *ctr, int blocks, hipStream_t s);
+// ... and those of batches of few rows only.
+__attribute__((weak)) hipError_t launch_fwd_few_batch(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
+                                                      hipStream_t s);
+__attribute__((weak)) hipError_t launch_inv_few_batch(const BatchItem *items, const int2 *tiles, int64_t n_tiles,
+                                                      unsigned lds, hipStream_t s);
 int fwd_batch_blocks_per_cu();
 int inv_batch_blocks_per_cu();
 int plan_single_stage(uint64_t n, uint32_t width, uint32_t levels, bool forward,
@@ -60,6 +65,8 @@ struct dwtfrag_batch {
   std::vector<BatchRun> runs;              // forward queue, then inverse queue
   int64_t n_fwd = 0, n_inv = 0;            // tiles per direction
   int64_t part_fwd = 0, part_inv = 0;      // of them with a partial last row
+  bool few_fwd = true, few_inv = true;     // every item is a view of few rows
+  unsigned few_lds = 0;                    // LDS of the inverse for them
   int fwd_blocks = 0, inv_blocks = 0;      // persistent grid per direction
   uint64_t off_ctr = 0, off_items = 0, off_runs = 0, off_tiles = 0, bytes = 0;
   char *dev = nullptr;                     // caller's device copy, set by upload
@@ -131,6 +138,9 @@ int plan_items(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_ent
     bi.out = src.out;
     bi.priv_bytes = priv_bytes;
     bi.levels = int32_t(src.levels);
+    b->few_fwd = b->few_fwd && few_rows(bi.fwd, bi.levels, kBatchCols, true);
+    b->few_inv = b->few_inv && few_rows(bi.inv, bi.levels, kBatchCols, false);
+    if (b->few_inv) b->few_lds = std::max(b->few_lds, inv_few_lds(bi.inv, bi.levels, kBatchCols));
     if (src.n % src.width) {
       b->part_fwd += bi.fwd.n_win;
       b->part_inv += bi.inv.n_win;
@@ -152,15 +162,16 @@ int plan_items(const dwtfrag_item *items, uint32_t count, const dwtfrag_tune_ent
 // pageable memory, which tile lists make common, stall a loop for 7 ms now and
 // then.
 void plan_queues(dwtfrag_batch *b) {
-  const auto tile_cost = [](const StageParams &P) {
+  const auto tile_cost = [](const StageParams &P, int halos) {
     const int64_t seg = int64_t(P.unit_rows) * ((P.units + P.n_seg - 1) / P.n_seg);
-    return std::min<int64_t>(P.H, seg + P.halo_t + P.halo_b) * std::min(P.W, P.own_w);
+    return std::min<int64_t>(P.H, seg + halos * P.halo_b) * std::min(P.W, P.own_w);
   };
   b->runs.reserve(2 * size_t(b->count));
   std::vector<std::pair<int64_t, int>> order(b->count);  // cost, item
   int64_t first = 0;
   for (const auto plan : {&BatchItem::fwd, &BatchItem::inv}) {
-    for (uint32_t i = 0; i < b->count; ++i) order[i] = {tile_cost(b->items[i].*plan), int(i)};
+    for (uint32_t i = 0; i < b->count; ++i) 
+      order[i] = {tile_cost(b->items[i].*plan, plan == &BatchItem::fwd ? 3 : 2), int(i)};
     std::stable_sort(order.begin(), order.end(),
                      [](const auto &x, const auto &y) { return x.first > y.first; });
     for (const auto &o : order) {
@@ -236,6 +247,9 @@ int dwtfrag_batch_protect(const dwtfrag_batch *b, void *stream) {
   BatchCounters *ctr = reinterpret_cast<BatchCounters *>(b->dev + b->off_ctr);
   const BatchItem *items = reinterpret_cast<const BatchItem *>(b->dev + b->off_items);
   const int2 *tiles = reinterpret_cast<const int2 *>(b->dev + b->off_tiles);
+  if (b->few_fwd && launch_fwd_few_batch && b->n_fwd <= kMaxLaunchWaves)
+    return launch_fwd_few_batch(items, tiles, b->n_fwd, static_cast<hipStream_t>(stream)) == hipSuccess
+               ? DWTFRAG_OK : DWTFRAG_EDEVICE;
   const int blocks = int(std::min<int64_t>(b->fwd_blocks, (b->n_fwd + kWavesPerBlock - 1) / kWavesPerBlock));
   const auto launch = launch_fwd_batch_tail && partial_rows_kernel(b->part_fwd, b->n_fwd, b->fwd_blocks, 200)
                           ? launch_fwd_batch_tail : launch_fwd_batch;
@@ -252,6 +266,9 @@ int dwtfrag_batch_restore(const dwtfrag_batch *b, void *stream) {
   BatchCounters *ctr = reinterpret_cast<BatchCounters *>(b->dev + b->off_ctr) + 1;
   const BatchItem *items = reinterpret_cast<const BatchItem *>(b->dev + b->off_items);
   const int2 *tiles = reinterpret_cast<const int2 *>(b->dev + b->off_tiles) + b->n_fwd;
+  if (b->few_inv && launch_inv_few_batch && b->n_inv <= kMaxLaunchWaves)
+    return launch_inv_few_batch(items, tiles, b->n_inv, b->few_lds, static_cast<hipStream_t>(stream)) == hipSuccess
+               ? DWTFRAG_OK : DWTFRAG_EDEVICE;
   const int blocks = int(std::min<int64_t>(b->inv_blocks, (b->n_inv + kWavesPerBlock - 1) / kWavesPerBlock));
   const auto launch = launch_inv_batch_tail && partial_rows_kernel(b->part_inv, b->n_inv, b->inv_blocks, 20)
                           ? launch_inv_batch_tail : launch_inv_batch;

@@ -181,7 +181,7 @@ struct AesLoad {
 };
 
 // Tables and key words together, for a block that uses one key.
-__device__ __forceinline__ void load_aes_tables(uint32_t *te, uint32_t *kw, const AesKey &key) {
+template <class K> __device__ __forceinline__ void load_aes_tables(uint32_t *te, uint32_t *kw, K &key) {
   load_aes_te(te);
   for (int i = threadIdx.x; i < kKeyWords; i += blockDim.x) kw[i] = key_word(key, i);
 }
@@ -201,7 +201,9 @@ struct StageParams {
   int32_t unit_rows, units;   // 2^L, ceil(H / 2^L)
   int32_t n_seg;              // number of row segments
   int32_t halo_l;             // columns before the owned range (multiple of lane_cols)
-  int32_t halo_t, halo_b;     // rows streamed before / after the owned range
+  int32_t block;              // wavefronts per workgroup of a launch of its own
+  int32_t halo_b;             // rows streamed after the owned range (before it: the
+                              // forward twice as many, the inverse as many)
   int32_t n_waves;
   int32_t use_aes;            // LL output / input goes through AES-CTR
   AesKey key;
@@ -276,6 +278,17 @@ __host__ __device__ constexpr int read_shift(int c0, int last, int span) {
 inline bool few_rows(const StageParams &P, int L, int C1, bool forward) {
   const bool slow = P.W % C1 != 0 || (forward && P.n_valid < int64_t(P.H) * P.W);
   return P.hdim[slow ? L : L - 1] == 1;
+}
+
+// LDS of a wavefront of the inverse of few rows: words per lane of level l's
+// rows (LL, HL, LH and HH), and bytes in all.
+__host__ __device__ constexpr int inv_few_words(int C1, int l, int rows) {
+  return 4 * ((C1 >> (l - 1)) >= 4 ? (C1 >> (l - 1)) / 4 : 1) * rows;
+}
+inline unsigned inv_few_lds(const StageParams &P, int L, int C1) {
+  unsigned words = 0;
+  for (int l = 1; l <= L; ++l) words += inv_few_words(C1, l, P.hdim[l]);
+  return 64 * 4 * words;
 }
 
 // First level-0 row of segment s (s == n_seg gives units * unit_rows).

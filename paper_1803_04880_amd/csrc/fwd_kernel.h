@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(4
 template <int L, int C1, bool U8IN, bool TAIL>
 hipError_t launch_fwd_t(const void *in, int16_t *pub, int16_t *llout, const StageParams &P,
                                hipStream_t s) {
-  const int per = block_waves(P.n_waves, device_cus());
+  const int per = P.block;
   hipLaunchKernelGGL((fwd_kernel<L, C1, U8IN, TAIL>), dim3((P.n_waves + per - 1) / per), dim3(64 * per), 0,
                      s, in, pub, llout, P);
   return hipGetLastError();

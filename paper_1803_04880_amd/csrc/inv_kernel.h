@@ -27,7 +27,7 @@ void inv_kernel(const int16_t *__restrict__ llin, const int16_t *__restrict__ pu
 template <int L, int C1, bool U8OUT, bool TAIL>
 hipError_t launch_inv_t(const int16_t *llin, const int16_t *pub, void *out,
                                const StageParams &P, hipStream_t s) {
-  const int per = block_waves(P.n_waves, device_cus());
+  const int per = P.block;
   hipLaunchKernelGGL((inv_kernel<L, C1, U8OUT, TAIL>), dim3((P.n_waves + per - 1) / per), dim3(64 * per), 0,
                      s, llin, pub, out, P);
   return hipGetLastError();

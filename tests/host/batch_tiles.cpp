@@ -22,9 +22,9 @@ int fwd_batch_blocks_per_cu() { return 2; }
 int inv_batch_blocks_per_cu() { return 2; }
 }  // namespace dwtfrag
 
-static int64_t cost(const StageParams &P) {
+static int64_t cost(const StageParams &P, bool forward) {
   const int64_t seg = int64_t(P.unit_rows) * ((P.units + P.n_seg - 1) / P.n_seg);
-  return std::min<int64_t>(P.H, seg + P.halo_t + P.halo_b) * std::min(P.W, P.own_w);
+  return std::min<int64_t>(P.H, seg + (forward ? 3 : 2) * P.halo_b) * std::min(P.W, P.own_w);
 }
 
 static std::vector<int2> sorted_tiles(const dwtfrag_batch &b, StageParams BatchItem::*plan) {
@@ -32,7 +32,7 @@ static std::vector<int2> sorted_tiles(const dwtfrag_batch &b, StageParams BatchI
   for (uint32_t i = 0; i < b.count; ++i)
     for (int w = 0; w < (b.items[i].*plan).n_waves; ++w) t.push_back(make_int2(int(i), w));
   std::vector<int64_t> c(b.count);
-  for (uint32_t i = 0; i < b.count; ++i) c[i] = cost(b.items[i].*plan);
+  for (uint32_t i = 0; i < b.count; ++i) c[i] = cost(b.items[i].*plan, plan == &BatchItem::fwd);
   std::stable_sort(t.begin(), t.end(), [&](const int2 &x, const int2 &y) { return c[x.x] > c[y.x]; });
   return t;
 }
