@@ -234,10 +234,14 @@ int plan_stage(const Geometry &g, int s, bool forward, const dwtfrag_launch *lau
     P->own_w = span - hl - hr;
     // A window owns whole lines of what it writes: lines that two windows
     // share are written in parts.  Forward: 128 bytes of its level-1 band rows
-    // (256 MiB at three levels: 448 of 512 columns 185 us, 496 columns 251
-    // us).  Inverse: 64 bytes of an output row (448 columns 165 us, 488: 172,
-    // 384: 170, each before rows loaded ahead were clamped), but at one level, where the cipher of the columns that
-    // windows share costs more, all it can (496 columns 253 us, 448: 276).
+    // (three levels at 8 columns a lane, 384 / 448 / 480 / 488 of 512 columns
+    // owned, us: 4 MiB 13.2 / 12.9 / 13.1 / 13.1, 16 MiB 19.1 / 19.4 / 18.2 /
+    // 18.1, 64 MiB 47.8 / 51.1 / 56.0 / 60.2, 256 MiB 157 / 174 / 203 / 227; two
+    // levels 16 MiB 16.2 / 16.8 / 18.0 / 20.9, 256 MiB 152 / 154 / 181 / 194).
+    // Inverse: 64 bytes of an output row (256 MiB at three levels: 448 columns
+    // 165 us, 488: 172, 384: 170, each before rows loaded ahead were clamped),
+    // but at one level, where the cipher of the columns that windows share costs
+    // more, all it can (496 columns 253 us, 448: 276).
     const int whole = forward ? 128 : L == 1 ? 1 : 64;
     P->own_w = P->own_w / whole * whole;
     P->n_win = (P->W + P->own_w - 1) / P->own_w;

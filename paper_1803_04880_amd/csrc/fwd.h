@@ -28,7 +28,8 @@
 // wavefront per long segment with LDS queues between the levels, which
 // waited for its own stores every batch: 256 MiB at three levels 231 -> 177
 // us (4.6 TB/s), 16 MiB 46.5 -> 18.4, 12 MB of width 3001 at two levels 65 ->
-// 20; one 16 MiB wavefront per SIMD issues for about 13 of its 18 us.
+// 25; at 16 MiB, where a wavefront has a SIMD to itself, it issues for 61% of
+// its 18 us.
 #pragma once
 
 #include "lift.h"

@@ -394,8 +394,8 @@ struct InvWavePk {
   }
   // The ring's loads, row k of HL, of LH and HH, of LL: from pointers that
   // move on while there is a next row (a row's address from its index is some
-  // ten scalar instructions, and a lone wavefront issues those one by one:
-  // 252 -> 157 a unit, 16 MiB at three levels 18.3 -> 17.4 us).
+  // ten scalar instructions, and a lone wavefront issues those one by one: 16
+  // MiB at three levels 18.3 -> 17.4 us).
   __device__ __forceinline__ static const char *advance(const char *p, bool more, int cols) {
     return uniform_ptr(p + (more ? 2u * uint32_t(cols) : 0u));
   }

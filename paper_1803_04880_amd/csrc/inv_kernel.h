@@ -5,6 +5,11 @@
 
 namespace dwtfrag {
 
+// Wavefronts per SIMD that the registers are to allow for: three at 16 columns
+// a lane, else four.  (At one level of 8 columns the keystreams' 42.5 KiB of LDS
+// a workgroup leave room for three, as the compiler warns.  With three asked for
+// it takes as many registers in another order: restore of 16 MiB 28.5 us, with
+// four 28.3.)
 template <int L, int C1, bool U8OUT, bool TAIL>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(C1 == 16 ? 3 : 4)))
 void inv_kernel(const int16_t *__restrict__ llin, const int16_t *__restrict__ pub,

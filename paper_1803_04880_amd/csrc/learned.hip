@@ -841,8 +841,12 @@ __global__ __launch_bounds__(64 * NW) void linv_level_kernel(LvCoef src, Dst dst
 // x 4096 at 4 / 8 / 16 wavefronts, us: 4096 tiles forward 75.5 / 76.8 / -,
 // inverse 96.6 / 88.6 / -; 1024 tiles 26.6 / 24.5 / 25.4 and 32.3 / 27.9 /
 // 28.2; 256 tiles 15.6 / 10.9 / 9.3 and 19.6 / 12.5 / 10.3.
-// Sixteen streams of such images, protect / restore of 64: 4 / 4 / 4 wavefronts
-// 4.64 / 5.58 ms, these 4.78 / 5.37, the inverse's 256 tiles at 16 5.67.
+// Several streams of such images, protect of 64, ms at 1 / 2 / 4 / 16 streams:
+// 4 / 4 / 4 wavefronts 7.52 / 5.33 / 4.23 / 4.43, these 6.96 / 4.98 / 4.38 /
+// 4.61 (4 / 4 / 8 7.23 / 5.54 / 4.37 / 4.57, 4 / 8 / 8 7.07 / 5.04 / 4.43 /
+// 4.61): one image waits less, four and more streams have their small levels
+// filled by each other.  Restore over sixteen 5.58 -> 5.37; the inverse's 256
+// tiles at 16 5.67.
 template <int N> struct Waves { static constexpr int value = N; };
 inline int fwd_level_waves(int64_t tiles) {
   const int cus = device_cus();
